@@ -376,64 +376,166 @@ __device__ __forceinline__ uint32_t finish_crc(uint32_t raw, uint32_t len,
   return len == kChunk ? raw ^ T.k_full : mat_apply(g.tail_mat, raw) ^ g.k_tail;
 }
 
-// -------------------------------------------------------------- checksum --
+// ------------------------------------------------- CRC on the matrix cores --
+// A chunk's CRC is a GF(2) matrix product: 524,288 bits by a 32-column
+// matrix.  The parity of an integer sum is its GF(2) sum, so 0/1 data bits
+// and 0/1 weights held as fp4 elements give it exactly on the matrix cores
+// (sums stay below 2^13, exact in their float accumulators).
+//
+// A lane's 16 bytes of a row are 32 nibbles; masking bit p of every nibble
+// gives 32 fp4 elements of plane p without any shift (0x1, 0x2, 0x4 are
+// 0.5, 1, 2; bit 3 is the sign, so (x & 0x8..) | 0x2.. is +-1), and the
+// weights (CrcTables::mc_b) are scaled to match.  One 32x32x64 product per
+// plane: the rows are the streams l % 32, the contracted index the nibbles
+// of both halves l / 32, the columns the register's 32 bits.  The weights
+// hold the shift to the end of the wave's share for row h, half, dword and
+// bit, so the eight rows of a share just accumulate: no dependent lookups,
+// and per 16 bytes and lane 16 VALU operations, four 16-byte LDS reads and
+// four products of 8 passes.  (The byte-table form of the same step takes
+// 24 VALU operations and sixteen 4-byte lookups in dependent rounds, and
+// 88 KiB of tables per workgroup against 38 KiB.)
+// The accumulators start at mc_bias, which puts every sum in [2^22, 2^23):
+// the float's last bit is then one half (never set) and the bit above it the
+// count's parity, all partial sums stay exact, and mc_fold packs 16 parities
+// with one shift per register, applies the lane's 16 columns of the shift
+// over the streams (mc_lane) and XORs the lanes.
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
 
-// Lane CRC values of a chunk, double-buffered by chunk step (low region).
-__device__ __forceinline__ uint32_t *chk_u(uint32_t b) {
-  return reinterpret_cast<uint32_t *>(lds_at(kLdsLow + b * (kThreads * 4u)));
+// LDS offsets from the tables' base: mc_b, mc_lane, mc_wave, mc_bias.
+constexpr uint32_t kMcLane = 32768, kMcWave = kMcLane + 4096, kMcBias = kMcWave + 1024;
+constexpr uint32_t kMcBytes = kMcBias + 256;
+
+template <uint32_t BASE>
+__device__ __forceinline__ void mc_load_tables(uint32_t kind) {
+  static_assert(offsetof(CrcTables, mc_lane) - offsetof(CrcTables, mc_b) == kMcLane &&
+                    offsetof(CrcTables, mc_wave) - offsetof(CrcTables, mc_b) == kMcWave &&
+                    offsetof(CrcTables, mc_bias) - offsetof(CrcTables, mc_b) == kMcBias &&
+                    offsetof(CrcTables, mc_b) % 16 == 0,
+                "mc_b .. mc_bias copied as one block");
+  const uint4 *src = reinterpret_cast<const uint4 *>(&g_tables[kind].mc_b[0][0][0]);
+  uint4 *dst = reinterpret_cast<uint4 *>(lds_at(BASE));
+  for (uint32_t i = threadIdx.x; i < kMcBytes / 16u; i += blockDim.x) dst[i] = src[i];
 }
 
-// Chunk CRCs: the eight data waves take chunk i's lane values while chunk
-// i+1 loads; the ninth wave folds chunk i-1's values into its CRC (the
-// Horner step over waves, then the lane shifts and their XOR).
+// The accumulators of a share before its first row.
+template <uint32_t BASE>
+__device__ __forceinline__ v16f mc_begin(uint32_t lane) {
+  const float b = *reinterpret_cast<const float *>(lds_at(BASE + kMcBias + 4u * lane));
+  return v16f{b, b, b, b, b, b, b, b, b, b, b, b, b, b, b, b};
+}
+
+// Row h of the wave's share enters the accumulators.
+template <uint32_t BASE>
+__device__ __forceinline__ void mc_row(v16f &acc, const uint4 &x, int h, uint32_t lane16) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    uint4 e;
+    if (p < 3) {
+      const uint32_t m = 0x11111111u << p;
+      e = make_uint4(x.x & m, x.y & m, x.z & m, x.w & m);
+    } else {
+      e = make_uint4((x.x & 0x88888888u) | 0x22222222u, (x.y & 0x88888888u) | 0x22222222u,
+                     (x.z & 0x88888888u) | 0x22222222u, (x.w & 0x88888888u) | 0x22222222u);
+    }
+    const uint4 w = *reinterpret_cast<const uint4 *>(lds_at(BASE + 1024u * (4 * h + p) + lane16));
+    const v8i A = {(int)e.x, (int)e.y, (int)e.z, (int)e.w, 0, 0, 0, 0};
+    const v8i B = {(int)w.x, (int)w.y, (int)w.z, (int)w.w, 0, 0, 0, 0};
+    acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, acc, 4, 4, 0, 0, 0, 0);
+  }
+}
+
+// The share's value (zero-init register, F^(kSub (7 - w)) still to come),
+// uniform over the wave.
+template <uint32_t BASE>
+__device__ __forceinline__ uint32_t mc_fold(const v16f &acc, uint32_t lane) {
+  uint32_t t = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const float f = acc[i];  // (a bit cast of the element itself reads element 0)
+    t = __builtin_amdgcn_alignbit(__builtin_bit_cast(uint32_t, f), t, 2);
+  }
+  uint32_t r = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint4 c = *reinterpret_cast<const uint4 *>(lds_at(BASE + kMcLane + 1024u * q + 16u * lane));
+    r = __builtin_amdgcn_bitop3_b32(c.x, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 1, 1), r, 0x6A);
+    r = __builtin_amdgcn_bitop3_b32(c.y, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 3, 1), r, 0x6A);
+    r = __builtin_amdgcn_bitop3_b32(c.z, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 5, 1), r, 0x6A);
+    r = __builtin_amdgcn_bitop3_b32(c.w, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 7, 1), r, 0x6A);
+  }
+  return wave_xor(r);
+}
+
+// The chunk's value from its eight shares' values v[w] (in LDS): 256 pairs
+// of a share and a bit, four per lane, each a column of F^(kSub (7 - w)).
+template <uint32_t BASE>
+__device__ __forceinline__ uint32_t mc_join(uint32_t v_lane, uint32_t lane) {
+  // v_lane: the value of share lane / 8
+  const uint4 c = *reinterpret_cast<const uint4 *>(lds_at(BASE + kMcWave + 16u * lane));
+  const uint32_t b = v_lane >> (4u * (lane & 7u));
+  uint32_t r = c.x & (0u - (b & 1u));
+  r = __builtin_amdgcn_bitop3_b32(c.y, (uint32_t)__builtin_amdgcn_sbfe((int)b, 1, 1), r, 0x6A);
+  r = __builtin_amdgcn_bitop3_b32(c.z, (uint32_t)__builtin_amdgcn_sbfe((int)b, 2, 1), r, 0x6A);
+  r = __builtin_amdgcn_bitop3_b32(c.w, (uint32_t)__builtin_amdgcn_sbfe((int)b, 3, 1), r, 0x6A);
+  return wave_xor(r);
+}
+
+// -------------------------------------------------------------- checksum --
+
+constexpr uint32_t kLdsChkPart = (kMcBytes + 255u) & ~255u;  // share values, two chunks
+constexpr uint32_t kLdsChecksum = kLdsChkPart + 2u * kWaves * 4u;
+
+// Chunk CRCs: each wave takes its share of chunk i while chunk i + 1 loads,
+// one barrier per chunk; wave i % 8 joins the shares of chunk i afterwards.
+// Bound by the HBM read: two workgroups fit a CU (38 KiB of LDS, at most 128
+// VGPRs), and the set-up is one 38 KiB copy.  1.67 GB in 251 us, 6,680 GB/s
+// (264 us with the byte tables, one workgroup per CU); 51 MB in 14.2 us
+// (17.4), 16 chunks in 6.4 us (10.0).
 // With `per_chunk` and chunks above 64 KiB, each tile's CRC is shifted past
 // the rest of its chunk and XORed into its chunk's entry (zeroed before the
 // launch): CRC(A|B) = F^|B|(CRC(A)) ^ CRC(B) is linear in the pieces' CRCs.
-__global__ __launch_bounds__(kThreads + 64) void k_checksum(
+__global__ __launch_bounds__(kThreads, 4) void k_checksum(
     const uint8_t *__restrict__ data, ChunkGeom g,
     uint32_t *__restrict__ crc_out, uint32_t per_chunk) {
-  load_crc_tables(g.crc_kind);
+  mc_load_tables<0>(g.crc_kind);
   __syncthreads();
   const CrcTables &T = g_tables[g.crc_kind];
-  const bool is_fold = threadIdx.x >= (uint32_t)kThreads;
-  const GLane gl = glane_make();
   const Lane l0 = lane_info();
   const uint32_t G = gridDim.x;
   const uint32_t my_n = blockIdx.x < g.n_chunks ? (g.n_chunks - 1 - blockIdx.x) / G + 1 : 0;
+  uint32_t *part = reinterpret_cast<uint32_t *>(lds_at(kLdsChkPart));
   uint4 d[kRows];
-  if (!is_fold)
-    load_chunk(data + (uint64_t)blockIdx.x * kChunk, my_n ? chunk_len(g, blockIdx.x) : 0u, l0, d);
-  for (uint32_t i = 0; i <= my_n; ++i) {
+  load_chunk(data + (uint64_t)blockIdx.x * kChunk, my_n ? chunk_len(g, blockIdx.x) : 0u, l0, d);
+  for (uint32_t i = 0; i < my_n; ++i) {
     const Lane l = lane_fresh(l0);
-    if (!is_fold) {
-      if (i < my_n) {
-        const uint32_t cn = blockIdx.x + (i + 1) * G;
-        const bool nv = i + 1 < my_n;
-        uint4 dn[kRows];
-        chk_u(i & 1)[l.wave * 64u + l.lane] =
-            lane_value_load(d, gl, data + (uint64_t)(nv ? cn : 0u) * kChunk,
-                            nv ? chunk_len(g, cn) : 0u, l, dn);
+    const uint32_t c = blockIdx.x + i * G, cn = c + G;
+    const bool nv = i + 1 < my_n;
+    const uint8_t *nbase = data + (uint64_t)(nv ? cn : 0u) * kChunk;
+    const uint32_t nlen = nv ? chunk_len(g, cn) : 0u;
+    uint4 dn[kRows];
+    load_chunk(nbase, nlen, l, dn);
+    v16f acc = mc_begin<0>(l.lane);
 #pragma unroll
-        for (int h = 0; h < kRows; ++h) d[h] = dn[h];
-      }
-    } else if (i >= 1) {
-      const uint32_t c = blockIdx.x + (i - 1) * G;
-      const uint32_t *u = chk_u((i - 1) & 1);
-      uint32_t acc = u[l.lane];
-#pragma unroll
-      for (int w = 1; w < kWaves; ++w) acc = tab4x(kLdsWaveStep, acc, u[w * 64 + l.lane]);
-      const uint32_t crc = finish_crc(lane_fold(acc), chunk_len(g, c), g, T);
+    for (int h = 0; h < kRows; ++h) mc_row<0>(acc, d[h], h, 16u * l.lane);
+    const uint32_t v = mc_fold<0>(acc, l.lane);
+    if (l.lane == 0) part[(i & 1u) * kWaves + l.wave] = v;
+    __syncthreads();
+    if (l.wave == (i & 7u)) {
+      const uint32_t crc = finish_crc(mc_join<0>(part[(i & 1u) * kWaves + (l.lane >> 3)], l.lane),
+                                      chunk_len(g, c), g, T);
       if (per_chunk && g.tile_log2) {
         const uint32_t big = c >> g.tile_log2;
         const uint64_t big_end = min((uint64_t)(big + 1) << (16 + g.tile_log2), g.nbytes);
         const uint64_t tile_end = min((uint64_t)(c + 1) * kChunk, g.nbytes);
-        const uint32_t part = shift_bytes(T, big_end - tile_end, crc);
-        if (l.lane == 0) atomicXor(&crc_out[big], part);
+        const uint32_t shifted = shift_bytes(T, big_end - tile_end, crc);
+        if (l.lane == 0) atomicXor(&crc_out[big], shifted);
       } else if (l.lane == 0) {
         crc_out[c] = crc;
       }
     }
-    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < kRows; ++h) d[h] = dn[h];
   }
 }
 
@@ -3481,7 +3583,7 @@ int set_kernel_attributes() {
                          reinterpret_cast<const void *>(&k_huf_encode<true>),
                          reinterpret_cast<const void *>(&k_huf_decode_w<false>),
                          reinterpret_cast<const void *>(&k_huf_decode_w<true>)};
-  const uint32_t bytes[8] = {kLdsBase,      kLdsEncode,     kLdsEncode,     kLdsDecode,
+  const uint32_t bytes[8] = {kLdsChecksum,  kLdsEncode,     kLdsEncode,     kLdsDecode,
                              kLdsHufEncode, kLdsHufEncode, kLdsHufDecodeW, kLdsHufDecodeW};
   for (int i = 0; i < 8; ++i) {
     hipError_t e = hipFuncSetAttribute(kern[i], hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -3538,8 +3640,8 @@ int launch_checksum(const void *data, const ChunkGeom &g, uint32_t *crc_out,
     if (e != hipSuccess) return (int)e;
   }
   if (g.n_chunks) {
-    uint32_t grid = min((uint32_t)n_cu, g.n_chunks);
-    hipLaunchKernelGGL(k_checksum, dim3(grid), dim3(kThreads + 64), kLdsBase, S(stream),
+    uint32_t grid = min((uint32_t)n_cu * 2u, g.n_chunks);
+    hipLaunchKernelGGL(k_checksum, dim3(grid), dim3(kThreads), kLdsChecksum, S(stream),
                        static_cast<const uint8_t *>(data), g, crc_out, per_chunk ? 1u : 0u);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;

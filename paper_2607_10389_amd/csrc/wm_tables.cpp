@@ -77,6 +77,46 @@ void byte_tables(const Mat &m, uint32_t out[4][256]) {
     for (uint32_t b = 0; b < 256; ++b) out[j][b] = apply(m, b << (8 * j));
 }
 
+// Tables of the matrix-core CRC.  A wave's row of 1 KiB is the A operand of
+// four 32x32x64 products, one per bit plane: lane l holds 16 bytes, 32
+// nibbles, and nibble e (dword e / 8) contributes its bit p.  The 32 rows of
+// the product are the streams s = l % 32; the two halves l / 32, 512 bytes
+// apart, and the nibbles are the 64 terms contracted with B, whose column n
+// is bit n of the 32-bit CRC register.
+void build_mc_tables(uint32_t poly, CrcTables *t) {
+  // fp4 (e2m1) codes of the weights that make every product 0 or 1 (planes
+  // 0..2, data elements 0.5, 1, 2) or +-0.5 (plane 3, data elements +-1)
+  const uint32_t code[4] = {4u, 2u, 1u, 1u};  // 2, 1, 0.5, 0.5
+  int k3[32] = {0};  // ones of plane 3's column n
+  for (int h = 0; h < kRows; ++h)
+    for (int half = 0; half < 2; ++half)
+      for (int j = 0; j < 4; ++j) {
+        const Mat m = byte_shift(poly, (int64_t)kRow * (kRows - 1 - h) + 512 * (1 - half) +
+                                           4 * (3 - j) + 4);
+        for (int b = 0; b < 32; ++b)
+          for (int n = 0; n < 32; ++n)
+            if ((m.c[b] >> n) & 1u) {
+              t->mc_b[4 * h + (b & 3)][32 * half + n][j] |= code[b & 3] << (4 * (b >> 2));
+              if ((b & 3) == 3) ++k3[n];
+            }
+      }
+  for (int l = 0; l < 64; ++l) {
+    // product register i of lane l: stream 8 (i / 4) + 4 (l / 32) + i % 4
+    for (int i = 0; i < 16; ++i) {
+      const int s = 8 * (i / 4) + 4 * (l / 32) + i % 4;
+      t->mc_lane[i / 4][l][i % 4] = apply(byte_shift(poly, 16 * (31 - s)), 1u << (l % 32));
+    }
+    // starting at 1.5 * 2^22 keeps the sums in [2^22, 2^23), where a float's last bit is
+    // one half and the bit above it the parity of the count; plane 3's
+    // constant half-sum is taken off
+    const float bias = 6291456.0f - 0.5f * (float)k3[l % 32];
+    std::memcpy(&t->mc_bias[l], &bias, 4);
+  }
+  for (int w = 0; w < kWaves; ++w)
+    std::memcpy(t->mc_wave[w], byte_shift(poly, (int64_t)kSub * (kWaves - 1 - w)).c,
+                sizeof(t->mc_wave[w]));
+}
+
 }  // namespace
 
 uint32_t poly_of(uint32_t crc_kind) {
@@ -111,6 +151,7 @@ void build_crc_tables(uint32_t poly, CrcTables *t) {
     p = compose(p, p);
   }
   t->k_full = apply(byte_shift(poly, kChunk), 0xFFFFFFFFu) ^ 0xFFFFFFFFu;
+  build_mc_tables(poly, t);
 }
 
 WsLayout ws_layout(uint32_t n_chunks) {

@@ -56,6 +56,33 @@ def test_ragged_checksum(wm, n):
     assert int(u32(m.global_crc)[0]) == g
 
 
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("fill", [0x00, 0xFF, 0x11, 0x22, 0x44, 0x88, 0xEE, "one bit", "random"])
+def test_checksum_bit_planes(wm, kind, fill):
+    """Chunk CRCs where the sums behind their parities are smallest and
+    largest (one bit plane of every nibble, all planes, none) and for single
+    bits, over more chunks than workgroups that fit the GPU (pipelined
+    chunks), with a short last chunk."""
+    n_chunks = 1200
+    n = n_chunks * CH - 4097
+    say(f"[checksum bit planes] kind={kind} fill={fill}")
+    if fill == "random":
+        data = random_bytes(n, seed=5)
+    else:
+        data = torch.full((n,), 0 if fill == "one bit" else fill, dtype=torch.uint8,
+                          device="cuda")
+    if fill == "one bit":  # chunk c has bit 437 c mod 524288 set
+        bit = torch.arange(n_chunks - 1, device="cuda") * 437 % (8 * CH)
+        data[torch.arange(n_chunks - 1, device="cuda") * CH + bit // 8] = \
+            (1 << (bit % 8)).to(torch.uint8)
+    m = mover(n, kind)
+    m.checksum(data)
+    torch.cuda.synchronize()
+    crcs, g = oracle.checksum_chunks(kind, host_bytes(data), CH, ORACLE_THREADS)
+    assert np.array_equal(m.crc_host(), crcs)
+    assert int(u32(m.global_crc)[0]) == g
+
+
 # The global CRC folds the n - 1 full chunks' CRCs in runs of four, 4096
 # pieces per pass over the workgroup (zeros padded in front): these counts
 # sit on either side of one and two passes.
