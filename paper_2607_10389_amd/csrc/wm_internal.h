@@ -40,12 +40,16 @@ struct CrcTables {
   // The matrix-core CRC (see the engine's comment in wm_kernels.hip).
   // mc_b[4 h + p][l]: lane l's 32 fp4 weights of bit plane p of row h;
   // mc_lane[q][l]: columns 4q..4q+3 of lane l's fold; mc_wave[w]: columns of
-  // F^(kSub (7 - w)); mc_bias[l]: the float added before the parity is read.
-  // mc_b .. mc_bias are copied to LDS as one block.
+  // F^(kSub (7 - w)); mc_bias[l]: the float the accumulators start from;
+  // mc_msg[l]: a 16-byte message's columns of bits 2l and 2l + 1.
+  // mc_b .. mc_msg are copied to LDS as one block.
   uint32_t mc_b[32][64][4];
   uint32_t mc_lane[4][64][4];
   uint32_t mc_wave[8][32];
   uint32_t mc_bias[64];
+  uint32_t mc_msg[64][2];
+  uint32_t k_msg16, k_msg12;     // F^16(~0) ^ ~0, F^12(~0) ^ ~0
+  uint32_t pad2_[2];
 };
 
 // Host-side table construction (wm_tables.cpp).

@@ -402,17 +402,18 @@ __device__ __forceinline__ uint32_t finish_crc(uint32_t raw, uint32_t len,
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// LDS offsets from the tables' base: mc_b, mc_lane, mc_wave, mc_bias.
+// LDS offsets from the tables' base: mc_b, mc_lane, mc_wave, mc_bias, mc_msg.
 constexpr uint32_t kMcLane = 32768, kMcWave = kMcLane + 4096, kMcBias = kMcWave + 1024;
-constexpr uint32_t kMcBytes = kMcBias + 256;
+constexpr uint32_t kMcMsg = kMcBias + 256, kMcBytes = kMcMsg + 512;
 
 template <uint32_t BASE>
 __device__ __forceinline__ void mc_load_tables(uint32_t kind) {
   static_assert(offsetof(CrcTables, mc_lane) - offsetof(CrcTables, mc_b) == kMcLane &&
                     offsetof(CrcTables, mc_wave) - offsetof(CrcTables, mc_b) == kMcWave &&
                     offsetof(CrcTables, mc_bias) - offsetof(CrcTables, mc_b) == kMcBias &&
+                    offsetof(CrcTables, mc_msg) - offsetof(CrcTables, mc_b) == kMcMsg &&
                     offsetof(CrcTables, mc_b) % 16 == 0,
-                "mc_b .. mc_bias copied as one block");
+                "mc_b .. mc_msg copied as one block");
   const uint4 *src = reinterpret_cast<const uint4 *>(&g_tables[kind].mc_b[0][0][0]);
   uint4 *dst = reinterpret_cast<uint4 *>(lds_at(BASE));
   for (uint32_t i = threadIdx.x; i < kMcBytes / 16u; i += blockDim.x) dst[i] = src[i];
@@ -428,6 +429,11 @@ __device__ __forceinline__ v16f mc_begin(uint32_t lane) {
 // Row h of the wave's share enters the accumulators.
 template <uint32_t BASE>
 __device__ __forceinline__ void mc_row(v16f &acc, const uint4 &x, int h, uint32_t lane16) {
+  // the two constants of plane 3 in registers: one three-input logic op
+  uint32_t c8 = 0x88888888u, c2 = 0x22222222u;
+  asm("" : "+s"(c8));
+  asm("" : "+v"(c2));
+  auto pm = [&](uint32_t v) { return __builtin_amdgcn_bitop3_b32(v, c8, c2, 0xEA); };
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     uint4 e;
@@ -435,8 +441,7 @@ __device__ __forceinline__ void mc_row(v16f &acc, const uint4 &x, int h, uint32_
       const uint32_t m = 0x11111111u << p;
       e = make_uint4(x.x & m, x.y & m, x.z & m, x.w & m);
     } else {
-      e = make_uint4((x.x & 0x88888888u) | 0x22222222u, (x.y & 0x88888888u) | 0x22222222u,
-                     (x.z & 0x88888888u) | 0x22222222u, (x.w & 0x88888888u) | 0x22222222u);
+      e = make_uint4(pm(x.x), pm(x.y), pm(x.z), pm(x.w));
     }
     const uint4 w = *reinterpret_cast<const uint4 *>(lds_at(BASE + 1024u * (4 * h + p) + lane16));
     const v8i A = {(int)e.x, (int)e.y, (int)e.z, (int)e.w, 0, 0, 0, 0};
@@ -479,6 +484,19 @@ __device__ __forceinline__ uint32_t mc_join(uint32_t v_lane, uint32_t lane) {
   r = __builtin_amdgcn_bitop3_b32(c.z, (uint32_t)__builtin_amdgcn_sbfe((int)b, 2, 1), r, 0x6A);
   r = __builtin_amdgcn_bitop3_b32(c.w, (uint32_t)__builtin_amdgcn_sbfe((int)b, 3, 1), r, 0x6A);
   return wave_xor(r);
+}
+
+// CRC of a 16-byte message of four uniform words (k = T.k_msg16), or of a
+// 12-byte one with w0 = 0 (k = T.k_msg12): lane l takes bits 2l and 2l + 1.
+// (A chain of 16 or 12 dependent table lookups otherwise.)
+template <uint32_t BASE>
+__device__ __forceinline__ uint32_t mc_msg(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3,
+                                           uint32_t k, uint32_t lane) {
+  const uint2 c = *reinterpret_cast<const uint2 *>(lds_at(BASE + kMcMsg + 8u * lane));
+  const uint32_t w = lane < 32u ? (lane < 16u ? w0 : w1) : (lane < 48u ? w2 : w3);
+  const uint32_t b = w >> (2u * (lane & 15u));
+  const uint32_t r = c.x & (0u - (b & 1u));
+  return wave_xor(__builtin_amdgcn_bitop3_b32(c.y, (uint32_t)__builtin_amdgcn_sbfe((int)b, 1, 1), r, 0x6A)) ^ k;
 }
 
 // -------------------------------------------------------------- checksum --
@@ -3142,9 +3160,8 @@ __global__ __launch_bounds__(kEncThreads) void k_huf_encode(EncArgs a, ChunkGeom
 // (table checks, code construction, the symbol-by-symbol decode of each
 // stream) overlap the other waves' work.  Lane l decodes streams q * 64 + l
 // (q = 0..7), which are its 16 bytes of rows 8q..8q+7 in the row layout: a
-// lane's output runs down rows 0..63 in order, so its four CRC column
-// streams take all 64 rows and the lane shifts and the XOR over the wave give
-// the record's CRC without a per-wave step.
+// group's eight rows are one share of the matrix-core CRC, whose value lane
+// q * 8 keeps until the shares join.
 // The 64 streams of group q are contiguous in the record; the wave copies
 // them into an LDS stage with coalesced loads issued one group ahead, and
 // each lane refills its bit buffer from the stage, so the decode waits on
@@ -3152,20 +3169,22 @@ __global__ __launch_bounds__(kEncThreads) void k_huf_encode(EncArgs a, ChunkGeom
 // load issued before it).  A group whose streams overflow the stage, and the
 // last, short record, take a per-symbol path.  Checks and verdict bits are
 // the same as the per-workgroup decoders'.
-constexpr int kHwWaves = 8;
+// Bound by latency (a table lookup in LDS per symbol) and, at 16 waves per
+// CU, by VALU issue (about 70% busy): so the CRC's 40 KiB of tables leave room
+// for 16 waves of 7.5 KiB (8 beside the byte tables' 90 KiB; a 3.5 KiB stage
+// holds streams of up to 6.8 bits a word), and an entry holds the symbol where
+// the word has it.  25,536 records (1.67 GB of bf16): 636 us (816 before),
+// 15 records: 51 us (58).
+constexpr int kHwWaves = 16;
 constexpr uint32_t kHwTab = 4096;    // per wave: decode table, 2^11 u16 entries
-constexpr uint32_t kHwStage = 4096;  // per wave: a group's streams (code order first)
-constexpr uint32_t kHwScratch = kHwTab + kHwStage;
+constexpr uint32_t kHwStage = 3584;  // per wave: a group's streams (code order first)
 constexpr uint32_t kHwOverrun = 64u * 11u / 8u + 8u;  // bytes a stream's reads may pass its end
-// waves 0..3 in the low region, waves 4..7 after the CRC tables; tables at
-// multiples of 4096, so an entry's address is the table's base ORed with it
-__device__ __forceinline__ uint32_t hw_scratch(uint32_t wave) {
-  return wave < 4u ? kLdsLow + wave * kHwScratch : kLdsBase + (wave - 4u) * kHwScratch;
-}
-constexpr uint32_t kLdsHufDecodeW = kLdsBase + 4u * kHwScratch;
-static_assert(4u * kHwScratch <= kLdsLowBytes && kLdsHufDecodeW <= 163840 &&
-                  kLdsBase % 4096u == 0 && kHwScratch % 4096u == 0,
-              "record-per-wave decoder LDS fits one CU");
+// the CRC tables, then the waves' decode tables (at multiples of 4096, so an
+// entry's address is the table's base ORed with it), then their stages
+constexpr uint32_t kLdsHwTab = (kMcBytes + 4095u) & ~4095u;
+constexpr uint32_t kLdsHwStage = kLdsHwTab + kHwWaves * kHwTab;
+constexpr uint32_t kLdsHufDecodeW = kLdsHwStage + kHwWaves * kHwStage;
+static_assert(kLdsHufDecodeW <= 163840, "record-per-wave decoder LDS fits one CU");
 
 __device__ __forceinline__ uint32_t buf4(Rsrc r, uint32_t off) {
   return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
@@ -3197,12 +3216,30 @@ __device__ __forceinline__ void words_from_planes(const uint2 &a, const uint2 &b
   }
 }
 
-// One row's words, CRC column steps and store, for rows that may pass the
-// chunk's end.
+// The decode table's entry of a code: its length in the low bits, and the
+// symbol where the word has it (format v2: the exponent at bits 7..14;
+// format v3: the high byte).
+template <bool V3>
+__device__ __forceinline__ uint32_t entry_of(uint32_t sym, uint32_t len) {
+  return (V3 ? sym << 8 : sym << 7) | len;
+}
+// Two words from their entries (low halves of e0, e1) and their plane-B
+// bytes j, j + 1 of b: each byte spread over its word, the symbol's bits
+// taken from the entries.
+template <bool V3>
+__device__ __forceinline__ uint32_t words_from_entries(uint32_t e0, uint32_t e1, uint32_t b,
+                                                       bool high) {
+  const uint32_t e = __builtin_amdgcn_perm(e1, e0, 0x05040100u);
+  const uint32_t s = __builtin_amdgcn_perm(0u, b, high ? 0x03030202u : 0x01010000u);
+  return bitsel(V3 ? 0xFF00FF00u : 0x7F807F80u, e, s);
+}
+
+// Row h (of a group of eight): its words, CRC products and store, for rows
+// that may pass the chunk's end.
 template <bool V3>
 __device__ __forceinline__ void hw_row_out(const uint2 &pa, const uint2 &pb, uint32_t w0,
                                            uint32_t n, bool full, uint32_t len, uint8_t *dst,
-                                           uint32_t (&cv)[4], const GLane &gl) {
+                                           v16f &cv, int h, uint32_t lane16) {
   uint32_t out[4];
   words_from_planes<V3>(pa, pb, out);
   if (!full && w0 + 8u > n) {  // words past the chunk's end are zero
@@ -3210,8 +3247,7 @@ __device__ __forceinline__ void hw_row_out(const uint2 &pa, const uint2 &pb, uin
     for (int j = 0; j < 8; ++j)
       if (w0 + j >= n) out[j >> 1] &= (j & 1) ? 0x0000FFFFu : 0xFFFF0000u;
   }
-#pragma unroll
-  for (int c = 0; c < 4; ++c) cv[c] = g_step(cv[c], out[c], gl);
+  mc_row<0>(cv, make_uint4(out[0], out[1], out[2], out[3]), h, lane16);
   dec_store(dst, 2u * w0, len, out);
 }
 
@@ -3226,16 +3262,21 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
   const uint32_t r_hi = min(r1, n_rec), r_lo = min(r0, r_hi);
   const uint64_t table_off = ((uint64_t)uniform((uint32_t)(ctl->table_off >> 32)) << 32) |
                              uniform((uint32_t)ctl->table_off);
-  load_crc_tables(g.crc_kind);
+  mc_load_tables<0>(g.crc_kind);
   __syncthreads();  // the only barrier: the tables are in LDS
   const CrcTables &T = g_tables[g.crc_kind];
-  const uint32_t wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63u;
-  const uint32_t tbase = hw_scratch(wave), sbase = tbase + kHwTab;
+  const uint32_t wave = uniform(threadIdx.x >> 6);
+  const uint32_t tbase = kLdsHwTab + wave * kHwTab, sbase = kLdsHwStage + wave * kHwStage;
   uint16_t *tab = reinterpret_cast<uint16_t *>(lds_at(tbase));
   uint8_t *sorted = lds_at(sbase);  // symbols in code order, while the table is built
-  const GLane gl = glane_make();
-  const unsigned long long below = (1ull << lane) - 1ull;
-  for (uint32_t r = r_lo + blockIdx.x * kHwWaves + wave; r < r_hi; r += gridDim.x * kHwWaves) {
+  // (a workgroup's waves take records a grid apart: few records spread over
+  // the CUs, a wave each, instead of filling the first ones)
+  for (uint32_t r = r_lo + blockIdx.x + gridDim.x * wave; r < r_hi; r += gridDim.x * kHwWaves) {
+    // (what derives from the lane is formed per record, not kept across them)
+    uint32_t lane = threadIdx.x & 63u;
+    asm volatile("" : "+v"(lane));
+    const uint32_t lane16 = 16u * lane;
+    const unsigned long long below = (1ull << lane) - 1ull;
     // ---- table entry (and its neighbours' chunk and offset) and header
     const uint8_t *e = payload + table_off + 16ull * r;
     uint32_t ew[4];
@@ -3251,7 +3292,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
     const bool tbad = c >= g.n_chunks || (r > 0 && prevc >= c) || (r == 0 && off != 64u) ||
                       (off & 15u) || off >= end || end > table_off ||
                       tile_order_bad(g, c, r == 0, has_next, nextc);
-    const uint32_t ec = crc_words(ew, 4);
+    const uint32_t ec = mc_msg<0>(ew[0], ew[1], ew[2], ew[3], T.k_msg16, lane);
     if (lane == 0) ecrc[r] = ec;
     if (tbad) {
       if (lane == 0) atomicOr(&ctl->table_bad, 1u);
@@ -3271,7 +3312,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
       k = (hw[0] >> 8) & 255u;
       base = (hw[0] >> 16) & 255u;
       sb = hw[2];
-      if (crc_words(hw, 3) != hw[3] || (hw[0] >> 24) || hw[1] != n) {
+      if (mc_msg<0>(0u, hw[0], hw[1], hw[2], T.k_msg12, lane) != hw[3] || (hw[0] >> 24) || hw[1] != n) {
         st = 4;
       } else if (mode == 0) {
         if (k || base || sb || rl != raw_rec_size(n)) st = 4;
@@ -3295,7 +3336,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
     // ---- code lengths, their checks and the decode table (HUF, k >= 1):
     // lane l holds symbols 2l, 2l+1 (nibble byte l) and 128+2l, 129+2l
     // (nibble byte 64 + l)
-    uint32_t so[8] = {0, 0, 0, 0, 0, 0, 0, 0}, sbq[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    uint2 sb8 = make_uint2(0, 0);  // the lane's eight streams' byte counts
     // the streams section (whole, with its padding: no load straddles its
     // end) and the first group's stage loads, in flight while the table is
     // built
@@ -3314,16 +3355,15 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
       }
       const uint32_t kraft = uniform(__builtin_amdgcn_readlane(wave_incl_scan(kr), 63));
       const uint32_t longest = uniform(wave_max(mx));
-      // stream byte counts and offsets: stream q * 64 + lane follows the
-      // streams before it
+      // stream byte counts and their total
       uint32_t tot = 0;
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        sbq[q] = rec[16 + 128 + q * 64 + lane];
-        const uint32_t incl = wave_incl_scan(sbq[q]);
-        so[q] = tot + incl - sbq[q];
-        tot += uniform(__builtin_amdgcn_readlane(incl, 63));
+        const uint32_t b = rec[16 + 128 + q * 64 + lane];
+        (q < 4 ? sb8.x : sb8.y) |= b << (8 * (q & 3));
+        tot += b;
       }
+      tot = uniform(__builtin_amdgcn_readlane(wave_incl_scan(tot), 63));
       bool hufbad = uniform(__ballot(bad) != 0) || kraft != (1u << kHufMaxLen) || longest != k ||
                     tot != sb;
 #pragma unroll
@@ -3363,7 +3403,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
           const uint32_t run = uniform(cnb[b] << (kHufMaxLen - b));
           for (uint32_t t = lane; t < run; t += 64u) {
             const uint32_t v = lb[b] + t;
-            tab[v] = (uint16_t)(b | ((uint32_t)sorted[stb[b] + (t >> (kHufMaxLen - b))] << 8));
+            tab[v] = (uint16_t)entry_of<V3>(sorted[stb[b] + (t >> (kHufMaxLen - b))], b);
           }
         }
         wave_sync();
@@ -3377,7 +3417,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
     const Rsrc rb = rsrc(rec + smo, (uint32_t)pad16(n));                       // plane B
     const Rsrc ra = rsrc(rec + 16, mode == 0 ? (uint32_t)pad16(n) : 0u);       // RAW plane A
     uint8_t *dst = staging + (uint64_t)r * kChunk;
-    uint32_t cv[4] = {0, 0, 0, 0};
+    uint32_t share = 0;  // the CRC value of group lane / 8's share
     const bool dec = hufk && hok;
     const bool full = n == kChunk / 2;
     if (!dec) {
@@ -3385,6 +3425,9 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
 #pragma unroll 1
       for (uint32_t q = 0; q < 8u; ++q) {
         uint2 pa[8], pb[8];
+        uint32_t l16 = lane16;  // (the weights' reads stay in the loop)
+        asm volatile("" : "+v"(l16));
+        v16f cv = mc_begin<0>(lane);
 #pragma unroll
         for (int h = 0; h < 8; ++h) {
           const uint32_t w0 = (8u * q + h) * 512u + 8u * lane;
@@ -3393,7 +3436,9 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
         }
 #pragma unroll
         for (int h = 0; h < 8; ++h)
-          hw_row_out<V3>(pa[h], pb[h], (8u * q + h) * 512u + 8u * lane, n, full, len, dst, cv, gl);
+          hw_row_out<V3>(pa[h], pb[h], (8u * q + h) * 512u + 8u * lane, n, full, len, dst, cv, h, l16);
+        const uint32_t v = mc_fold<0>(cv, lane);
+        share = (lane >> 3) == q ? v : share;
       }
     } else {
       // ---- Huffman streams: group q's bytes [A, A + 4096) staged as 4 KiB
@@ -3401,18 +3446,23 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
       // flight while this one decodes and enter the stage after it
       const uint32_t s4 = k <= 8u ? 1u : 0u;  // 4 symbols per refill check, else 2
       const uint32_t *stg = reinterpret_cast<const uint32_t *>(lds_at(sbase));
-      uint32_t A = 0;  // group 0 starts the section
+      uint32_t A = 0;    // group 0 starts the section
+      uint32_t sob = 0;  // the group's first byte
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        *reinterpret_cast<uint4 *>(lds_at(sbase + 1024u * i + 16u * lane)) = sq0[i];
+        if (1024u * i + lane16 < kHwStage)
+          *reinterpret_cast<uint4 *>(lds_at(sbase + 1024u * i + lane16)) = sq0[i];
       wave_sync();
 #pragma unroll 1
       for (uint32_t q = 0; q < 8u; ++q) {
-        const uint32_t soq = so[q], sbl = sbq[q];
+        // stream q * 64 + lane follows the streams before it
+        const uint32_t sbl = ((q < 4u ? sb8.x : sb8.y) >> (8u * (q & 3u))) & 255u;
+        const uint32_t incl = wave_incl_scan(sbl), soq = sob + incl - sbl;
+        sob += uniform(__builtin_amdgcn_readlane(incl, 63));  // the next group's
         // in the stage, with room for the reads of a stream that overruns
         // its bytes (64 codes of at most 11 bits and a dword ahead)
         const bool fits =
-            uniform(__builtin_amdgcn_readlane(soq + sbl, 63)) - A <= kHwStage - kHwOverrun;
+            sob - A <= kHwStage - kHwOverrun;
         const bool more = q < 7u;
         uint2 pb[8];
 #pragma unroll
@@ -3420,7 +3470,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
         uint4 sq[4];
         uint32_t an = 0;
         if (more) {
-          an = uniform(__builtin_amdgcn_readlane(so[q + 1u], 0)) & ~15u;
+          an = sob & ~15u;
 #pragma unroll
           for (int i = 0; i < 4; ++i) sq[i] = buf16(rs, an + 1024u * i + 16u * lane);
         }
@@ -3432,6 +3482,9 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
         // must fill exactly the stream's bytes
         uint64_t acc;
         int32_t nb;
+        uint32_t l16 = lane16;
+        asm volatile("" : "+v"(l16));
+        v16f cv = mc_begin<0>(lane);
         uint32_t pos = soq - A;
         const uint32_t pos0 = pos;
         if (fits && full) {
@@ -3445,12 +3498,13 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
           nb = (int32_t)(32u - 8u * (pos & 3u));
           ra += 4u;
           uint32_t nxt = lds_u32(ra);
-          // nb is kept in the low byte of nbx, from which whole entries
-          // (length | symbol << 8) are subtracted; the next dword enters below
-          // the nb bits held when fewer than 32 are
+          // nb is kept in the low seven bits of nbx, from which whole entries
+          // (the length in their low bits, the symbol above bit 6) are
+          // subtracted; the next dword enters below the nb bits held when
+          // fewer than 32 are
           int32_t nbx = nb;
           auto refill = [&]() {
-            const int32_t nbv = nbx & 255;
+            const int32_t nbv = nbx & 127;
             nbx = nbv;
             if (nbv < 32) {
               const uint32_t x = __builtin_bitreverse32(nxt);
@@ -3469,48 +3523,33 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
             nbx -= (int32_t)ent;
             return ent;
           };
-          // symbols (byte 1 of four entries) into one dword
-          auto pack4 = [](uint32_t e0, uint32_t e1, uint32_t e2, uint32_t e3) -> uint32_t {
-            return __builtin_amdgcn_perm(e1, e0, 0x0C0C0501u) |
-                   (__builtin_amdgcn_perm(e3, e2, 0x0C0C0501u) << 16);
-          };
-          auto row = [&](int h, const uint32_t (&a8)[2]) {
-            uint32_t out[4];
-            words_from_planes<V3>(make_uint2(a8[0], a8[1]), pb[h], out);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) cv[c] = g_step(cv[c], out[c], gl);
+          auto row = [&](int h, const uint32_t (&w)[4]) {
+            mc_row<0>(cv, make_uint4(w[0], w[1], w[2], w[3]), h, l16);
             *reinterpret_cast<uint4 *>(dst + 2u * ((8u * q + h) * 512u + 8u * lane)) =
-                make_uint4(out[0], out[1], out[2], out[3]);
+                make_uint4(w[0], w[1], w[2], w[3]);
           };
-          if (s4) {
+          auto rows = [&](auto four_c) {
+            constexpr bool kFour = decltype(four_c)::value;
 #pragma unroll
             for (int h = 0; h < 8; ++h) {
-              uint32_t a8[2];
+              uint32_t w[4];
 #pragma unroll
               for (int j = 0; j < 2; ++j) {
-                refill();
-                const uint32_t x0 = symbol(), x1 = symbol(), x2 = symbol(), x3 = symbol();
-                a8[j] = pack4(x0, x1, x2, x3);
-              }
-              row(h, a8);
-            }
-          } else {
-#pragma unroll
-            for (int h = 0; h < 8; ++h) {
-              uint32_t a8[2];
-#pragma unroll
-              for (int j = 0; j < 2; ++j) {
+                const uint32_t b = j ? pb[h].y : pb[h].x;
                 refill();
                 const uint32_t x0 = symbol(), x1 = symbol();
-                refill();
+                if (!kFour) refill();
                 const uint32_t x2 = symbol(), x3 = symbol();
-                a8[j] = pack4(x0, x1, x2, x3);
+                w[2 * j] = words_from_entries<V3>(x0, x1, b, false);
+                w[2 * j + 1] = words_from_entries<V3>(x2, x3, b, true);
               }
-              row(h, a8);
+              row(h, w);
             }
-          }
+          };
+          if (s4) rows(BoolC<true>{});
+          else rows(BoolC<false>{});
           pos = ra - sbase;
-          nb = nbx & 255;
+          nb = nbx & 127;
         } else {
           // per symbol: words past the chunk's end have none; bytes from the
           // stage, or from the record where the group overflows it
@@ -3536,11 +3575,15 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
                 const uint32_t ln = ent & 15u;
                 acc <<= ln;
                 nb -= (int32_t)ln;
-                a8[j >> 2] |= (ent >> 8) << (8 * (j & 3));
+                a8[j >> 2] |= ((ent >> (V3 ? 8 : 7)) & 255u) << (8 * (j & 3));
               }
             }
-            hw_row_out<V3>(make_uint2(a8[0], a8[1]), pb[h], w0, n, full, len, dst, cv, gl);
+            hw_row_out<V3>(make_uint2(a8[0], a8[1]), pb[h], w0, n, full, len, dst, cv, h, l16);
           }
+        }
+        {
+          const uint32_t v = mc_fold<0>(cv, lane);
+          share = (lane >> 3) == q ? v : share;
         }
         // exactly the stream's bytes, the last one's unused bits zero
         const uint32_t used = 8u * (pos - pos0) - (uint32_t)nb;
@@ -3550,7 +3593,8 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
           wave_sync();
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<uint4 *>(lds_at(sbase + 1024u * i + 16u * lane)) = sq[i];
+            if (1024u * i + lane16 < kHwStage)
+              *reinterpret_cast<uint4 *>(lds_at(sbase + 1024u * i + lane16)) = sq[i];
           wave_sync();
           A = an;
         }
@@ -3565,7 +3609,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
         rec[kHufHead + sb + lane - 32u])
       bad = true;
     // ---- the record's CRC against its receipt
-    const uint32_t crc = finish_crc(lane_fold(lane_merge(cv[0], cv[1], cv[2], cv[3])), len, g, T);
+    const uint32_t crc = finish_crc(mc_join<0>(share, lane), len, g, T);
     const uint32_t stf = __ballot(bad) ? 4u : (crc != ew[1] ? 8u : 0u);
     if (lane == 0) {
       if (rec_status) rec_status[r] = stf;
@@ -4058,7 +4102,7 @@ int launch_decode_records_v2(const void *payload, const ChunkGeom &g, void *stag
                              uint32_t r0, uint32_t r1, void *stream) {
   if (r1 <= r0 || !g.n_chunks) return 0;
   const uint32_t recs = min(r1 - r0, g.n_chunks);
-  const uint32_t grid = min((uint32_t)n_cu, (recs + kHwWaves - 1u) / kHwWaves);
+  const uint32_t grid = min((uint32_t)n_cu, recs);
   if (g.codec == 3)
     hipLaunchKernelGGL(k_huf_decode_w<true>, dim3(grid), dim3(64 * kHwWaves), kLdsHufDecodeW,
                        S(stream), static_cast<const uint8_t *>(payload), g,

@@ -112,6 +112,11 @@ void build_mc_tables(uint32_t poly, CrcTables *t) {
     const float bias = 6291456.0f - 0.5f * (float)k3[l % 32];
     std::memcpy(&t->mc_bias[l], &bias, 4);
   }
+  for (int l = 0; l < 64; ++l)  // bits 2l, 2l + 1: of word l / 16
+    for (int i = 0; i < 2; ++i)
+      t->mc_msg[l][i] = apply(byte_shift(poly, 16 - 4 * (l / 16)), 1u << (2 * (l % 16) + i));
+  t->k_msg16 = apply(byte_shift(poly, 16), 0xFFFFFFFFu) ^ 0xFFFFFFFFu;
+  t->k_msg12 = apply(byte_shift(poly, 12), 0xFFFFFFFFu) ^ 0xFFFFFFFFu;
   for (int w = 0; w < kWaves; ++w)
     std::memcpy(t->mc_wave[w], byte_shift(poly, (int64_t)kSub * (kWaves - 1 - w)).c,
                 sizeof(t->mc_wave[w]));

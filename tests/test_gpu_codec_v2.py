@@ -324,3 +324,26 @@ def test_v2_precopy_rounds(wm, codec):
     st, nd = m.precopy_round(cur, shipped, dest)
     assert st == wm.WM_OK
     assert torch.equal(dest, cur.view(-1).view(torch.uint8))
+
+
+@pytest.mark.parametrize("symbols", [90, 108, 128, 200])
+def test_wide_streams(wm, codec, symbols):
+    """Plane A uniform over `symbols` values: streams on either side of what
+    the decoder's stage holds (54 bytes each) and of the RAW limit."""
+    rng = np.random.default_rng(symbols)
+    n = 4 * CH // 2 + 2000
+    a = rng.integers(20, 20 + symbols, n)
+    b = rng.integers(0, 256, n)
+    w = (a << 8 | b) if codec == 3 else ((b >> 7) << 15 | a << 7 | (b & 127))
+    ship(wm, w.astype(np.uint16).view(np.uint8), 0, f"{symbols} symbols", codec)
+
+
+@pytest.mark.parametrize("records", [1, 255, 257, 4095, 4097])
+def test_record_per_wave_counts(wm, codec, records):
+    """Record counts around the CU count and the waves of the whole grid; the
+    last record short."""
+    n = records * CH - 2 * (records % 1000)
+    say(f"[v{codec}] {records} records, {n} bytes")
+    spec = wm_inputs.CacheSpec("waves", (1, 2, 1, -(-n // 512), 128), seed=records)
+    state = host_bytes(wm_inputs.make_cache(spec, "cuda"))[:n].copy()
+    ship(wm, state, 1, f"{records} records", codec)
