@@ -210,10 +210,10 @@ wm_status encode_tiles(const void *state, const ChunkGeom &g, const uint32_t *id
 }
 
 // wm_encode_step for chunks above 64 KiB: dirtiness is the chunk's (any
-// tile differs), so there is no single pass; the diff gives the dirty chunk
-// list, every tile is checksummed (chunk CRCs fold from tile CRCs, and the
-// global CRC covers every tile), and the list encoder ships the dirty
-// chunks' tiles.  Without prev every chunk ships from one encoding pass.
+// tile differs), so there is no single pass; one pass over the state and the
+// snapshot gives the dirty chunk list and every tile's CRC (chunk CRCs fold
+// from tile CRCs, and the global CRC covers every tile), and the list encoder
+// ships the dirty chunks' tiles.  Without prev every chunk ships from one encoding pass.
 wm_status encode_step_tiles(const void *cur, const void *prev, const ChunkGeom &g,
                             uint32_t *crc_out, uint32_t *global_crc, uint32_t *dirty_idx,
                             uint32_t *n_dirty, void *payload, uint64_t *payload_bytes, void *ws,
@@ -234,9 +234,8 @@ wm_status encode_step_tiles(const void *cur, const void *prev, const ChunkGeom &
   }
   uint32_t *list = dirty_idx ? dirty_idx : t.chunks;
   uint32_t *n_list = n_dirty ? n_dirty : t.n_chunks;
-  if (launch_diff(cur, prev, g, list, n_list, ws, L, stream) != 0 ||
+  if (launch_scan(cur, prev, g, unit_crc, list, n_list, ws, L, n_cu, stream) != 0 ||
       launch_expand_list(list, n_list, g, t.tiles, t.n_tiles, stream) != 0 ||
-      launch_checksum(cur, g, unit_crc, nullptr, n_cu, stream, true) != 0 ||
       (crc_out && launch_fold_tiles(unit_crc, g, crc_out, stream) != 0))
     return WM_ERR_HIP;
   if (g.codec != WM_CODEC_EXPFOR)
@@ -390,19 +389,20 @@ wm_status encode_step_call(const void *cur, const void *prev, uint64_t nbytes,
   uint8_t *wsb = static_cast<uint8_t *>(ws);
   uint32_t *crcs = crc_out ? crc_out : reinterpret_cast<uint32_t *>(wsb + L.flags);
   if (g.codec != WM_CODEC_EXPFOR) {
-    // format v2 has no single-pass encoder: the same outputs from the diff
-    // (whose flags it consumes first), a checksum of every chunk and the
-    // list encoder, each reading the state once
+    // format v2 has no single-pass step: the dirty list and every chunk's
+    // CRC from one pass over the state and the snapshot, then the list
+    // encoder.  Without a snapshot the encoder's own read gives the CRCs.
+    if (!prev) {
+      if ((dirty_idx || n_dirty) && launch_fill_all(dirty_idx, n_dirty, g.n_chunks, stream) != 0)
+        return WM_ERR_HIP;
+      return hip_status(launch_encode_v2(cur, g, nullptr, nullptr, nullptr, crcs, global_crc,
+                                         payload, payload_bytes, ws, L, n_cu, stream));
+    }
     uint32_t *list = dirty_idx ? dirty_idx : reinterpret_cast<uint32_t *>(wsb + list_offset(L, g.n_chunks));
     uint32_t *n_list = n_dirty ? n_dirty : list + g.n_chunks;
-    if (prev && launch_diff(cur, prev, g, list, n_list, ws, L, stream) != 0) return WM_ERR_HIP;
-    if (!prev && (dirty_idx || n_dirty) &&
-        launch_fill_all(dirty_idx, n_dirty, g.n_chunks, stream) != 0)
-      return WM_ERR_HIP;
-    if (launch_checksum(cur, g, crcs, nullptr, n_cu, stream) != 0) return WM_ERR_HIP;
-    return hip_status(launch_encode_v2(cur, g, prev ? list : nullptr, prev ? n_list : nullptr,
-                                       crcs, nullptr, global_crc, payload, payload_bytes, ws, L,
-                                       n_cu, stream));
+    if (launch_scan(cur, prev, g, crcs, list, n_list, ws, L, n_cu, stream) != 0) return WM_ERR_HIP;
+    return hip_status(launch_encode_v2(cur, g, list, n_list, crcs, nullptr, global_crc, payload,
+                                       payload_bytes, ws, L, n_cu, stream));
   }
   return hip_status(launch_encode(2, cur, prev, g, nullptr, nullptr, nullptr, crcs, global_crc,
                                   dirty_idx, n_dirty, payload, payload_bytes, ws, L, n_cu,

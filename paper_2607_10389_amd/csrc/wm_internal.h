@@ -117,6 +117,10 @@ int launch_checksum(const void *data, const ChunkGeom &g, uint32_t *crc_out,
 int launch_diff(const void *cur, const void *prev, const ChunkGeom &g,
                 uint32_t *dirty_idx, uint32_t *n_dirty, void *ws,
                 const WsLayout &L, void *stream);
+// launch_diff, and the CRC of every unit of cur, from one pass.
+int launch_scan(const void *cur, const void *prev, const ChunkGeom &g, uint32_t *unit_crc,
+                uint32_t *dirty_idx, uint32_t *n_dirty, void *ws, const WsLayout &L, int n_cu,
+                void *stream);
 // Chunks above 64 KiB: a device list of the caller's chunks as the list of
 // their tiles (an invalid list as an over-long one), and chunk CRCs from
 // tile CRCs.

@@ -501,8 +501,8 @@ __device__ __forceinline__ uint32_t mc_msg(uint32_t w0, uint32_t w1, uint32_t w2
 
 // -------------------------------------------------------------- checksum --
 
-constexpr uint32_t kLdsChkPart = (kMcBytes + 255u) & ~255u;  // share values, two chunks
-constexpr uint32_t kLdsChecksum = kLdsChkPart + 2u * kWaves * 4u;
+constexpr uint32_t kLdsChkPart = (kMcBytes + 255u) & ~255u;  // share values (and diff flags), two chunks
+constexpr uint32_t kLdsChecksum = kLdsChkPart + 4u * kWaves * 4u;
 
 // Chunk CRCs: each wave takes its share of chunk i while chunk i + 1 loads,
 // one barrier per chunk; wave i % 8 joins the shares of chunk i afterwards.
@@ -554,6 +554,80 @@ __global__ __launch_bounds__(kThreads, 4) void k_checksum(
     }
 #pragma unroll
     for (int h = 0; h < kRows; ++h) d[h] = dn[h];
+  }
+}
+
+// The checksum and the diff in one pass: chunk CRCs of cur, and flags[c] = 1
+// for each chunk that differs from prev.  Bound by the HBM read of both.
+// A row of either state is consumed and the next chunk's row loaded into the
+// same registers at once, so that each wave keeps about 15 of its 16 loads
+// in flight and nothing is copied.
+__global__ __launch_bounds__(kThreads, 4) void k_scan(const uint8_t *__restrict__ cur,
+                                                      const uint8_t *__restrict__ prev,
+                                                      ChunkGeom g, uint32_t *__restrict__ crc_out,
+                                                      uint32_t *__restrict__ flags) {
+  mc_load_tables<0>(g.crc_kind);
+  const CrcTables &T = g_tables[g.crc_kind];
+  const Lane l0 = lane_info();
+  const uint32_t G = gridDim.x;
+  const uint32_t my_n = blockIdx.x < g.n_chunks ? (g.n_chunks - 1 - blockIdx.x) / G + 1 : 0;
+  uint32_t *part = reinterpret_cast<uint32_t *>(lds_at(kLdsChkPart));
+  uint4 d[kRows], p[kRows];
+  auto load_rows = [&](uint32_t c, uint32_t len, const Lane &l, int h) {
+    const uint8_t *bd = cur + (uint64_t)c * kChunk, *bp = prev + (uint64_t)c * kChunk;
+    d[h] = buf16<kNt>(rsrc(bd, len), l.off0 + h * kRow);
+    p[h] = buf16<kNt>(rsrc(bp, len), l.off0 + h * kRow);
+  };
+  // a short chunk's straddling piece, as in load_chunk
+  auto patch = [&](uint32_t c, uint32_t len, const Lane &l) {
+    if (len & 15u) {
+#pragma unroll
+      for (int h = 0; h < kRows; ++h) {
+        const uint32_t off = l.off0 + h * kRow;
+        if (off < len && off + 16u > len) {
+          d[h] = load16_partial(cur + (uint64_t)c * kChunk + off, len - off);
+          p[h] = load16_partial(prev + (uint64_t)c * kChunk + off, len - off);
+        }
+      }
+    }
+  };
+  const uint32_t len0 = my_n ? chunk_len(g, blockIdx.x) : 0u;
+#pragma unroll
+  for (int h = 0; h < kRows; ++h) load_rows(my_n ? blockIdx.x : 0u, len0, l0, h);
+  patch(blockIdx.x, len0, l0);
+  __syncthreads();
+  for (uint32_t i = 0; i < my_n; ++i) {
+    const Lane l = lane_fresh(l0);
+    const uint32_t c = blockIdx.x + i * G;
+    const bool nv = i + 1 < my_n;
+    const uint32_t cn = nv ? c + G : 0u, nlen = nv ? chunk_len(g, cn) : 0u;
+    v16f acc = mc_begin<0>(l.lane);
+    uint32_t df = 0;
+#pragma unroll
+    for (int h = 0; h < kRows; ++h) {
+      __builtin_amdgcn_sched_barrier(0);
+      df |= (d[h].x ^ p[h].x) | (d[h].y ^ p[h].y) | (d[h].z ^ p[h].z) | (d[h].w ^ p[h].w);
+      asm volatile("" : "+v"(df));  // (taken here, not gathered at the end)
+      mc_row<0>(acc, d[h], h, 16u * l.lane);
+      load_rows(cn, nlen, l, h);
+    }
+    const uint32_t v = mc_fold<0>(acc, l.lane);
+    const unsigned long long any = __ballot(df != 0);
+    patch(cn, nlen, l);
+    if (l.lane == 0) {
+      part[(i & 1u) * kWaves + l.wave] = v;
+      part[(2u + (i & 1u)) * kWaves + l.wave] = any ? 1u : 0u;
+    }
+    __syncthreads();
+    if (l.wave == (i & 7u)) {
+      const uint32_t crc = finish_crc(mc_join<0>(part[(i & 1u) * kWaves + (l.lane >> 3)], l.lane),
+                                      chunk_len(g, c), g, T);
+      const unsigned long long dirty = __ballot(part[(2u + (i & 1u)) * kWaves + (l.lane & 7u)] != 0);
+      if (l.lane == 0) {
+        crc_out[c] = crc;
+        flags[c] = dirty ? 1u : 0u;
+      }
+    }
   }
 }
 
@@ -3619,7 +3693,8 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
 }
 
 int set_kernel_attributes() {
-  const void *kern[8] = {reinterpret_cast<const void *>(&k_checksum),
+  const void *kern[9] = {reinterpret_cast<const void *>(&k_checksum),
+                         reinterpret_cast<const void *>(&k_scan),
                          reinterpret_cast<const void *>(&k_encode<false>),
                          reinterpret_cast<const void *>(&k_encode<true>),
                          reinterpret_cast<const void *>(&k_decode),
@@ -3627,9 +3702,9 @@ int set_kernel_attributes() {
                          reinterpret_cast<const void *>(&k_huf_encode<true>),
                          reinterpret_cast<const void *>(&k_huf_decode_w<false>),
                          reinterpret_cast<const void *>(&k_huf_decode_w<true>)};
-  const uint32_t bytes[8] = {kLdsChecksum,  kLdsEncode,     kLdsEncode,     kLdsDecode,
+  const uint32_t bytes[9] = {kLdsChecksum, kLdsChecksum,  kLdsEncode,     kLdsEncode, kLdsDecode,
                              kLdsHufEncode, kLdsHufEncode, kLdsHufDecodeW, kLdsHufDecodeW};
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < 9; ++i) {
     hipError_t e = hipFuncSetAttribute(kern[i], hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)bytes[i]);
     if (e != hipSuccess) return (int)e;
@@ -3764,6 +3839,25 @@ int launch_diff(const void *cur, const void *prev, const ChunkGeom &g, uint32_t 
     hipLaunchKernelGGL(k_diff, dim3(grid), dim3(256), 0, S(stream),
                        static_cast<const uint8_t *>(cur), static_cast<const uint8_t *>(prev), g,
                        flags);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
+  hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, S(stream), flags, g.hdr_n, g.tile_log2,
+                     g.n_chunks, dirty_idx, n_dirty);
+  return (int)hipGetLastError();
+}
+
+// The flags lie where the look-back words of the encode that follows will
+// (it clears them), so that the CRCs may lie in the flag array.
+int launch_scan(const void *cur, const void *prev, const ChunkGeom &g, uint32_t *unit_crc,
+                uint32_t *dirty_idx, uint32_t *n_dirty, void *ws, const WsLayout &L, int n_cu,
+                void *stream) {
+  uint32_t *flags = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(ws) + L.status);
+  if (g.n_chunks) {
+    const uint32_t grid = min((uint32_t)n_cu * 2u, g.n_chunks);
+    hipLaunchKernelGGL(k_scan, dim3(grid), dim3(kThreads), kLdsChecksum, S(stream),
+                       static_cast<const uint8_t *>(cur), static_cast<const uint8_t *>(prev), g,
+                       unit_crc, flags);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
   }

@@ -347,3 +347,28 @@ def test_record_per_wave_counts(wm, codec, records):
     spec = wm_inputs.CacheSpec("waves", (1, 2, 1, -(-n // 512), 128), seed=records)
     state = host_bytes(wm_inputs.make_cache(spec, "cuda"))[:n].copy()
     ship(wm, state, 1, f"{records} records", codec)
+
+
+@pytest.mark.parametrize("chunks", [1, 3, 511, 513, 1100])
+@pytest.mark.parametrize("tail", [2, 14, 18, 1024, 65534, 65536])
+def test_step_scan_dirty_list_and_crcs(wm, chunks, tail):
+    """The dirty list and the CRCs of a format v2 step (one pass over both
+    states) where one byte differs: the first or last of a chunk, or any of
+    a lane's row edges, over less and more than the grid's chunks."""
+    n = (chunks - 1) * 65536 + tail
+    gen = torch.Generator(device="cuda").manual_seed(chunks + tail)
+    prev = torch.randint(0, 256, (n,), generator=gen, device="cuda", dtype=torch.uint8)
+    cur = prev.clone()
+    spots = [0, 65535, 1023, 1024, 8191, 8192, 40961]
+    for i, c in enumerate(range(0, chunks, 5)):
+        at = c * 65536 + spots[i % len(spots)]
+        cur[min(at, n - 1)] ^= 0x80
+    cur[n - 1] ^= 1  # the tail's last byte
+    m = mover(n, kind=chunks & 1)
+    m.encode_step(cur, prev)
+    torch.cuda.synchronize()
+    hc, hp = cur.cpu().numpy(), prev.cpu().numpy()
+    crcs, g = oracle.checksum_chunks(chunks & 1, hc)
+    assert np.array_equal(m.crc_host(), crcs)
+    assert int(m.global_crc.cpu().numpy().view("uint32")[0]) == g
+    assert np.array_equal(m.dirty_host(), oracle.diff_dirty(hc, hp))
