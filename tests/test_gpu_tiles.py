@@ -289,3 +289,20 @@ def test_production_in_4mib_chunks(wm, codec):
     assert m.commit(live, scatter=True) == 0
     torch.cuda.synchronize()
     assert torch.equal(live, cur)
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("chunk,tiles,tail", [(1 << 17, 3, 2), (1 << 22, 65, 65534),
+                                              (1 << 23, 128, 65536), (1 << 23, 128 + 65, 4098),
+                                              (1 << 24, 256 + 2, 16)])
+def test_chunk_crcs_fold_from_tiles(wm, kind, chunk, tiles, tail):
+    """Chunk CRCs of a full ship (folded from the tiles' CRCs) with fewer,
+    exactly 64 and more tiles per chunk, the last tile short."""
+    nbytes = (tiles - 1) * TILE + tail
+    state = bf16_state(nbytes, seed=tiles + kind)
+    m = mover(nbytes, kind, chunk)
+    m.encode_step(state, None)
+    torch.cuda.synchronize()
+    crcs, g = oracle.checksum_chunks(kind, host_bytes(state), chunk)
+    assert np.array_equal(m.crc_host(), crcs)
+    assert int(u32(m.global_crc)[0]) == g
