@@ -668,8 +668,7 @@ wm_status wm_precopy_round(const void *cur, void *shipped, void *dest, uint64_t 
   n_cu = stream_cus(stream, n_cu);
   if (nbytes) {
     // both installs are conditional on the same device verdict word
-    if (launch_commit(dest, g, b->staging, b->payload, b->verdict, n_cu, stream) != 0 ||
-        launch_commit(shipped, g, b->staging, b->payload, b->verdict, n_cu, stream) != 0)
+    if (launch_commit(dest, g, b->staging, b->payload, b->verdict, n_cu, stream, shipped) != 0)
       return WM_ERR_HIP;
   }
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);

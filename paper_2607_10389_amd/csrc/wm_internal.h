@@ -151,9 +151,10 @@ int launch_decode_records(const void *payload, const ChunkGeom &g, void *staging
                           uint32_t r0, uint32_t r1, void *stream);
 int launch_decode_end(const ChunkGeom &g, uint32_t *verdict, void *ws, const WsLayout &L,
                       void *stream);
+// The records into live and, if given, into live2 as well.
 int launch_commit(void *live, const ChunkGeom &g, const void *staging,
                   const void *payload, const uint32_t *verdict, int n_cu,
-                  void *stream);
+                  void *stream, void *live2 = nullptr);
 // idx[i] = i for i < n (idx may be NULL) and *n_out = n (n_out may be NULL).
 int launch_fill_all(uint32_t *idx, uint32_t *n_out, uint32_t n, void *stream);
 // Re-verification before an install: CRCs of live's chunks (geometry g) and

@@ -142,3 +142,24 @@ def test_rounds_while_the_source_keeps_writing(wm):
     assert torch.equal(dest, cur.view(-1).view(torch.uint8))
     assert torch.equal(shipped, dest)
     assert rounds[-1]["dirty"] == 0
+
+
+@pytest.mark.parametrize("tail", [2, 17 * 2, 65534, 65536])
+def test_a_round_installs_into_both_states(wm, tail):
+    """The records of a round in dest and in shipped, a short last chunk
+    among them; the bytes after the states stay."""
+    from paper_2607_10389_amd import Mover
+    n = 40 * CH + tail
+    gen = torch.Generator(device="cuda").manual_seed(tail)
+    cur = torch.randint(0, 256, (n,), generator=gen, device="cuda", dtype=torch.uint8)
+    room = [torch.full((n + 64,), 7, device="cuda", dtype=torch.uint8) for _ in range(2)]
+    shipped, dest = (r[:n] for r in room)
+    m = Mover(n)
+    for k in range(2):
+        st, nd = m.precopy_round(cur, shipped, dest)
+        assert st == wm.WM_OK and nd == (41 if k == 0 else 15)
+        assert torch.equal(dest, cur) and torch.equal(shipped, cur)
+        assert all(bool((r[n:] == 7).all()) for r in room)
+        for c in range(0, 41, 3):
+            cur[c * CH + 5] ^= 1
+        cur[n - 1] ^= 1
