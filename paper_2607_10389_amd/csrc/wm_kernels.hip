@@ -513,22 +513,31 @@ constexpr uint32_t kLdsChecksum = kLdsChkPart + 4u * kWaves * 4u;
 // With `per_chunk` and chunks above 64 KiB, each tile's CRC is shifted past
 // the rest of its chunk and XORed into its chunk's entry (zeroed before the
 // launch): CRC(A|B) = F^|B|(CRC(A)) ^ CRC(B) is linear in the pieces' CRCs.
+// LIST: only the chunks of an ascending list, list[g.n_chunks] of them (a
+// chunk's index is read two chunks ahead of its bytes).
+template <bool LIST>
 __global__ __launch_bounds__(kThreads, 4) void k_checksum(
     const uint8_t *__restrict__ data, ChunkGeom g,
-    uint32_t *__restrict__ crc_out, uint32_t per_chunk) {
+    uint32_t *__restrict__ crc_out, uint32_t per_chunk, const uint32_t *__restrict__ list) {
   mc_load_tables<0>(g.crc_kind);
   __syncthreads();
   const CrcTables &T = g_tables[g.crc_kind];
   const Lane l0 = lane_info();
   const uint32_t G = gridDim.x;
-  const uint32_t my_n = blockIdx.x < g.n_chunks ? (g.n_chunks - 1 - blockIdx.x) / G + 1 : 0;
+  const uint32_t n = LIST ? ld_const(list + g.n_chunks) : g.n_chunks;
+  const uint32_t my_n = blockIdx.x < n ? (n - 1 - blockIdx.x) / G + 1 : 0;
+  auto item = [&](uint32_t i) {  // this workgroup's i-th chunk
+    const uint32_t at = blockIdx.x + i * G;
+    return !LIST ? at : (i < my_n ? ld_const(list + at) : 0u);
+  };
   uint32_t *part = reinterpret_cast<uint32_t *>(lds_at(kLdsChkPart));
   uint4 d[kRows];
-  load_chunk(data + (uint64_t)blockIdx.x * kChunk, my_n ? chunk_len(g, blockIdx.x) : 0u, l0, d);
+  uint32_t c = item(0), cn = item(1);
+  load_chunk(data + (uint64_t)(my_n ? c : 0u) * kChunk, my_n ? chunk_len(g, c) : 0u, l0, d);
   for (uint32_t i = 0; i < my_n; ++i) {
     const Lane l = lane_fresh(l0);
-    const uint32_t c = blockIdx.x + i * G, cn = c + G;
     const bool nv = i + 1 < my_n;
+    const uint32_t cnn = item(i + 2);
     const uint8_t *nbase = data + (uint64_t)(nv ? cn : 0u) * kChunk;
     const uint32_t nlen = nv ? chunk_len(g, cn) : 0u;
     uint4 dn[kRows];
@@ -554,6 +563,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_checksum(
     }
 #pragma unroll
     for (int h = 0; h < kRows; ++h) d[h] = dn[h];
+    c = cn;
+    cn = cnn;
   }
 }
 
@@ -3709,7 +3720,8 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
 }
 
 int set_kernel_attributes() {
-  const void *kern[9] = {reinterpret_cast<const void *>(&k_checksum),
+  const void *kern[10] = {reinterpret_cast<const void *>(&k_checksum<false>),
+                         reinterpret_cast<const void *>(&k_checksum<true>),
                          reinterpret_cast<const void *>(&k_scan),
                          reinterpret_cast<const void *>(&k_encode<false>),
                          reinterpret_cast<const void *>(&k_encode<true>),
@@ -3718,9 +3730,9 @@ int set_kernel_attributes() {
                          reinterpret_cast<const void *>(&k_huf_encode<true>),
                          reinterpret_cast<const void *>(&k_huf_decode_w<false>),
                          reinterpret_cast<const void *>(&k_huf_decode_w<true>)};
-  const uint32_t bytes[9] = {kLdsChecksum, kLdsChecksum,  kLdsEncode,     kLdsEncode, kLdsDecode,
+  const uint32_t bytes[10] = {kLdsChecksum, kLdsChecksum, kLdsChecksum, kLdsEncode,     kLdsEncode, kLdsDecode,
                              kLdsHufEncode, kLdsHufEncode, kLdsHufDecodeW, kLdsHufDecodeW};
-  for (int i = 0; i < 9; ++i) {
+  for (int i = 0; i < 10; ++i) {
     hipError_t e = hipFuncSetAttribute(kern[i], hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)bytes[i]);
     if (e != hipSuccess) return (int)e;
@@ -3776,8 +3788,9 @@ int launch_checksum(const void *data, const ChunkGeom &g, uint32_t *crc_out,
   }
   if (g.n_chunks) {
     uint32_t grid = min((uint32_t)n_cu * 2u, g.n_chunks);
-    hipLaunchKernelGGL(k_checksum, dim3(grid), dim3(kThreads), kLdsChecksum, S(stream),
-                       static_cast<const uint8_t *>(data), g, crc_out, per_chunk ? 1u : 0u);
+    hipLaunchKernelGGL(k_checksum<false>, dim3(grid), dim3(kThreads), kLdsChecksum, S(stream),
+                       static_cast<const uint8_t *>(data), g, crc_out, per_chunk ? 1u : 0u,
+                       static_cast<const uint32_t *>(nullptr));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
   }
@@ -4093,8 +4106,51 @@ int launch_fill_all(uint32_t *idx, uint32_t *n_out, uint32_t n, void *stream) {
 }
 
 // ------------------------------------------------------------- reverify --
+// The chunks of live that the payload's records do not overwrite, as an
+// ascending list (idx[n_chunks] is its length): only their CRCs enter the
+// resulting state's.  The table of a verified payload is strictly ascending;
+// one that is not (changed since) lists every chunk.  Wave w of the single
+// workgroup writes the gaps before records w, w + 16, ...: chunk c between
+// records r - 1 and r has c - r uncovered chunks before it.
+__global__ __launch_bounds__(1024) void k_uncovered(const uint8_t *__restrict__ payload,
+                                                    uint32_t n_chunks, uint32_t *__restrict__ idx) {
+  const uint32_t n_rec = ld_u32(payload + 24);
+  const uint8_t *table = payload + ld_u64(payload + 32) - 16ull * n_rec;
+  auto chunk_of = [&](uint32_t r) { return ld_u32(table + 16ull * r); };
+  bool bad = n_rec > n_chunks;
+  if (!bad)
+    for (uint32_t r = threadIdx.x; r < n_rec; r += 1024u) {
+      const uint32_t c = chunk_of(r);
+      bad = bad || c >= n_chunks || (r > 0 && chunk_of(r - 1) >= c);
+    }
+  bad = __syncthreads_or(bad);
+  if (bad) {
+    for (uint32_t c = threadIdx.x; c < n_chunks; c += 1024u) idx[c] = c;
+  } else {
+    const uint32_t lane = threadIdx.x & 63u;
+    // lane l takes the gap before record r + l; gaps longer than a few
+    // chunks are written by the whole wave
+    for (uint32_t r0 = (threadIdx.x >> 6) * 64u; r0 <= n_rec; r0 += 1024u) {
+      const uint32_t r = r0 + lane;
+      uint32_t lo = 0, hi = 0;  // the gap [lo, hi)
+      if (r <= n_rec) {
+        lo = r ? chunk_of(r - 1) + 1u : 0u;
+        hi = r < n_rec ? chunk_of(r) : n_chunks;
+      }
+      if (hi - lo <= 4u)
+        for (uint32_t c = lo; c < hi; ++c) idx[c - r] = c;
+      for (unsigned long long m = __ballot(hi - lo > 4u); m; m &= m - 1u) {
+        const int j = __builtin_ctzll(m);
+        const uint32_t l2 = __builtin_amdgcn_readlane(lo, j), h2 = __builtin_amdgcn_readlane(hi, j);
+        for (uint32_t c = l2 + lane; c < h2; c += 64u) idx[c - (r0 + j)] = c;
+      }
+    }
+  }
+  if (threadIdx.x == 0) idx[n_chunks] = bad ? n_chunks : n_chunks - n_rec;
+}
+
 // Re-verifying install (Table 1: commit re-verifies, then swaps).  live_crc
-// holds the CRC of every chunk of live, staged_crc that of every staged
+// holds the CRC of every chunk of live that no record overwrites, staged_crc that of every staged
 // record.  One workgroup walks the payload's table: a staged record whose
 // CRC differs from its receipt sets the flag, and the record's receipt
 // replaces the CRC of the chunk it will overwrite, so that live_crc becomes
@@ -4135,8 +4191,20 @@ int launch_reverify(const void *live, const ChunkGeom &g, const void *staging,
   uint32_t *live_crc = reinterpret_cast<uint32_t *>(wsb + L.flags);
   uint32_t *staged_crc = reinterpret_cast<uint32_t *>(wsb + L.entry_crc);
   uint32_t *words = reinterpret_cast<uint32_t *>(wsb + L.ctl);  // [0] flag, [1] global
-  int rc = launch_checksum(live, g, live_crc, nullptr, n_cu, stream, true);
-  if (rc) return rc;
+  int rc = 0;
+  if (g.n_chunks) {
+    // (the list lies where the look-back words and the staged table would)
+    uint32_t *list = reinterpret_cast<uint32_t *>(wsb + L.status);
+    hipLaunchKernelGGL(k_uncovered, dim3(1), dim3(1024), 0, S(stream),
+                       static_cast<const uint8_t *>(payload), g.n_chunks, list);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+    hipLaunchKernelGGL(k_checksum<true>, dim3(min((uint32_t)n_cu * 2u, g.n_chunks)), dim3(kThreads),
+                       kLdsChecksum, S(stream), static_cast<const uint8_t *>(live), g, live_crc, 0u,
+                       list);
+    e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
   rc = launch_checksum(staging, gs, staged_crc, nullptr, n_cu, stream, true);
   if (rc) return rc;
   hipLaunchKernelGGL(k_reverify_records, dim3(1), dim3(1024), 0, S(stream),

@@ -126,3 +126,42 @@ def test_reverify_production_step(wm):
     assert m.commit_reverify(live) == wm.WM_VERIFY_FAILED
     assert int(m.verdict.item()) == wm.V_REVERIFY
     assert torch.equal(live, before)
+
+
+@pytest.mark.parametrize("n_chunks,dirty", [
+    (1, []), (1, [0]), (40, [0]), (40, [39]), (40, list(range(0, 40, 2))), (40, list(range(40))),
+    (70, [5, 6, 7, 68]), (1500, [0, 3, 9, 700, 1499]), (1500, list(range(0, 1500, 6))),
+    (1500, list(range(1, 1500)))])
+def test_reverify_reads_the_chunks_that_stay(wm, n_chunks, dirty):
+    """Gaps of every kind between the installed records (none, short, longer
+    than a wave, the ends): a flipped byte in any chunk that stays is seen,
+    one in a chunk that is overwritten does not matter."""
+    from paper_2607_10389_amd import Mover
+    n = (n_chunks - 1) * CH + 4098
+    prev, cur = _pair(n_chunks + len(dirty), n, dirty)
+    m = Mover(n)
+    m.encode_step(cur, prev)
+    m.decode()
+    torch.cuda.synchronize()
+    assert m.dirty_host().tolist() == dirty
+    live = prev.clone()
+    for c in dirty:
+        live[c * CH + 77] ^= 4
+    _check(m, live, 0, wm.WM_OK, "overwritten chunks differ")
+    assert torch.equal(live, cur)
+    stay = sorted(set(range(n_chunks)) - set(dirty))
+    for c in sorted(set(stay[:2] + stay[len(stay) // 2:][:1] + stay[-2:])):
+        m.verdict.zero_()
+        live = prev.clone()
+        live[min(c * CH + CH - 1, n - 1)] ^= 1
+        before = live.clone()
+        _check(m, live, 0, wm.WM_VERIFY_FAILED, f"chunk {c}")
+        assert torch.equal(live, before)
+    if len(dirty) > 2:  # the table changed after the verdict, out of order
+        m.verdict.zero_()
+        at = int(m.payload_bytes.item()) - 16 * len(dirty)
+        t = m.payload[at:at + 32].clone()
+        m.payload[at:at + 16], m.payload[at + 16:at + 32] = t[16:], t[:16]
+        live = prev.clone()
+        _check(m, live, 0, wm.WM_VERIFY_FAILED, "table out of order")
+        assert torch.equal(live, prev)
