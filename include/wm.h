@@ -77,9 +77,10 @@ typedef int32_t wm_status;
  * exponent's lowest bit and the mantissa, close to 8 bits of entropy) raw.
  * All fall back to RAW per chunk.  Every call takes any format, except
  * wm_encode_step_static (format v1 only).  Formats v2 and v3 have no
- * single-pass encoder: their wm_encode_step runs the diff, a checksum of
- * every chunk and the list encoder (same outputs), and their pre-copy rounds
- * checksum every chunk. */
+ * single-pass step: their wm_encode_step takes the dirty list and every
+ * chunk's CRC from one read of cur and prev, then runs the list encoder (same
+ * outputs; without prev the encoder's own read gives the CRCs), and their
+ * pre-copy rounds checksum every chunk. */
 #define WM_CODEC_EXPFOR 1
 #define WM_CODEC_EXPHUF 2
 #define WM_CODEC_BYTEPLANE 3
@@ -189,8 +190,9 @@ wm_status wm_encode(const void *state, uint64_t nbytes, const wm_params *p,
  *   global_crc : 1 u32, or NULL
  *   dirty_idx  : n_chunks u32, or NULL;  n_dirty : 1 u32, or NULL
  * Chunks above 64 KiB: a chunk is dirty when any of its tiles differs and
- * then ships whole, so with prev the call runs the diff, a checksum of every
- * tile and the list encoder (same outputs, more reads) instead of one pass.
+ * then ships whole, so with prev the call takes the dirty list and every
+ * tile's CRC from one read of cur and prev and then runs the list encoder
+ * (same outputs, more reads) instead of one pass.
  * Other arguments as wm_encode. */
 wm_status wm_encode_step(const void *cur, const void *prev, uint64_t nbytes,
                          const wm_params *p, uint32_t *crc_out,
