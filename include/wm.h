@@ -265,7 +265,7 @@ wm_status wm_commit_or_abort(void *live, uint64_t nbytes, const wm_params *p,
  *     state: the destination's base is the source's last shipped snapshot.
  * Without it the guarantee of a dirty ship holds only relative to the base
  * the destination already had.  On failure WM_V_REVERIFY is ORed into
- * *verdict and live is untouched.  Costs a read of live and of the staged
+ * *verdict and live is untouched.  Costs a read of those chunks and of the staged
  * records (their CRCs) before the install.  Waits for the stream; returns
  * WM_OK (installed) or WM_VERIFY_FAILED.
  *   live, staging, payload, verdict : as for wm_commit_or_abort (SCATTER)
