@@ -372,3 +372,23 @@ def test_step_scan_dirty_list_and_crcs(wm, chunks, tail):
     assert np.array_equal(m.crc_host(), crcs)
     assert int(m.global_crc.cpu().numpy().view("uint32")[0]) == g
     assert np.array_equal(m.dirty_host(), oracle.diff_dirty(hc, hp))
+
+
+@pytest.mark.parametrize("order", ["first", "last", "alternate"])
+def test_uneven_groups(wm, codec, order):
+    """Chunks whose eight groups of 64 streams differ most in length: most at
+    one bit a word, others at eight to ten (their streams pass the
+    decoder's stage), at the record's start, at its end and by turns."""
+    rng = np.random.default_rng(5)
+    wide = {"first": [0], "last": [7], "alternate": [1, 4, 6]}[order]
+    chunks = []
+    for c in range(3):
+        a = np.where(rng.random(CH // 2) < 0.97, 60, 61)
+        for q in wide:
+            a[4096 * q:4096 * (q + 1)] = 70 + rng.integers(0, 120, 4096)
+        b = rng.integers(0, 256, CH // 2)
+        chunks.append((a << 8 | b) if codec == 3 else ((b >> 7) << 15 | a << 7 | (b & 127)))
+    state = np.concatenate(chunks)[: 5 * CH // 4 + 3000].astype(np.uint16).view(np.uint8)
+    for kind in (0, 1):
+        got, _ = ship(wm, state, kind, f"uneven groups {order}", codec)
+        assert got[64] == 2  # the first record is Huffman-coded
