@@ -42,7 +42,7 @@ struct CrcTables {
   // mc_lane[q][l]: columns 4q..4q+3 of lane l's fold; mc_wave[w]: columns of
   // F^(kSub (7 - w)); mc_bias[l]: the float the accumulators start from;
   // mc_msg[l]: a 16-byte message's columns of bits 2l and 2l + 1.
-  // mc_b .. mc_msg are copied to LDS as one block.
+  // mc_b .. mc_bias are copied to LDS as one block (the Huffman decoder: mc_b).
   uint32_t mc_b[32][64][4];
   uint32_t mc_lane[4][64][4];
   uint32_t mc_wave[8][32];

@@ -402,28 +402,32 @@ __device__ __forceinline__ uint32_t finish_crc(uint32_t raw, uint32_t len,
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// LDS offsets from the tables' base: mc_b, mc_lane, mc_wave, mc_bias, mc_msg.
+// LDS offsets from the tables' base: mc_b, mc_lane, mc_wave, mc_bias.
 constexpr uint32_t kMcLane = 32768, kMcWave = kMcLane + 4096, kMcBias = kMcWave + 1024;
-constexpr uint32_t kMcMsg = kMcBias + 256, kMcBytes = kMcMsg + 512;
+constexpr uint32_t kMcBytes = kMcBias + 256;
 
-template <uint32_t BASE>
+// BYTES: all of them, or mc_b alone (kMcLane).
+template <uint32_t BASE, uint32_t BYTES = kMcBytes>
 __device__ __forceinline__ void mc_load_tables(uint32_t kind) {
   static_assert(offsetof(CrcTables, mc_lane) - offsetof(CrcTables, mc_b) == kMcLane &&
                     offsetof(CrcTables, mc_wave) - offsetof(CrcTables, mc_b) == kMcWave &&
                     offsetof(CrcTables, mc_bias) - offsetof(CrcTables, mc_b) == kMcBias &&
-                    offsetof(CrcTables, mc_msg) - offsetof(CrcTables, mc_b) == kMcMsg &&
+                    offsetof(CrcTables, mc_msg) - offsetof(CrcTables, mc_b) == kMcBytes &&
                     offsetof(CrcTables, mc_b) % 16 == 0,
-                "mc_b .. mc_msg copied as one block");
+                "mc_b .. mc_bias copied as one block");
   const uint4 *src = reinterpret_cast<const uint4 *>(&g_tables[kind].mc_b[0][0][0]);
   uint4 *dst = reinterpret_cast<uint4 *>(lds_at(BASE));
-  for (uint32_t i = threadIdx.x; i < kMcBytes / 16u; i += blockDim.x) dst[i] = src[i];
+  for (uint32_t i = threadIdx.x; i < BYTES / 16u; i += blockDim.x) dst[i] = src[i];
 }
 
 // The accumulators of a share before its first row.
+__device__ __forceinline__ v16f mc_start(uint32_t bias) {
+  const float b = __builtin_bit_cast(float, bias);
+  return v16f{b, b, b, b, b, b, b, b, b, b, b, b, b, b, b, b};
+}
 template <uint32_t BASE>
 __device__ __forceinline__ v16f mc_begin(uint32_t lane) {
-  const float b = *reinterpret_cast<const float *>(lds_at(BASE + kMcBias + 4u * lane));
-  return v16f{b, b, b, b, b, b, b, b, b, b, b, b, b, b, b, b};
+  return mc_start(*reinterpret_cast<const uint32_t *>(lds_at(BASE + kMcBias + 4u * lane)));
 }
 
 // Row h of the wave's share enters the accumulators.
@@ -450,34 +454,43 @@ __device__ __forceinline__ void mc_row(v16f &acc, const uint4 &x, int h, uint32_
   }
 }
 
-// The share's value (zero-init register, F^(kSub (7 - w)) still to come),
-// uniform over the wave.
-template <uint32_t BASE>
-__device__ __forceinline__ uint32_t mc_fold(const v16f &acc, uint32_t lane) {
+// The lane's 16 parities of a share: bit 2 i + 1 for register i, zeros between.
+__device__ __forceinline__ uint32_t mc_parities(const v16f &acc) {
   uint32_t t = 0;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const float f = acc[i];  // (a bit cast of the element itself reads element 0)
     t = __builtin_amdgcn_alignbit(__builtin_bit_cast(uint32_t, f), t, 2);
   }
+  return t;
+}
+// The share's value (zero-init register, F^(kSub (7 - w)) still to come),
+// uniform over the wave, from the parities at bits 2 i + AT and the lane's
+// columns col(0..3) (CrcTables::mc_lane).
+template <int AT, class Col>
+__device__ __forceinline__ uint32_t mc_share(uint32_t t, const Col &col) {
   uint32_t r = 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const uint4 c = *reinterpret_cast<const uint4 *>(lds_at(BASE + kMcLane + 1024u * q + 16u * lane));
-    r = __builtin_amdgcn_bitop3_b32(c.x, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 1, 1), r, 0x6A);
-    r = __builtin_amdgcn_bitop3_b32(c.y, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 3, 1), r, 0x6A);
-    r = __builtin_amdgcn_bitop3_b32(c.z, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 5, 1), r, 0x6A);
-    r = __builtin_amdgcn_bitop3_b32(c.w, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 7, 1), r, 0x6A);
+    const uint4 c = col(q);
+    r = __builtin_amdgcn_bitop3_b32(c.x, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + AT, 1), r, 0x6A);
+    r = __builtin_amdgcn_bitop3_b32(c.y, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 2 + AT, 1), r, 0x6A);
+    r = __builtin_amdgcn_bitop3_b32(c.z, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 4 + AT, 1), r, 0x6A);
+    r = __builtin_amdgcn_bitop3_b32(c.w, (uint32_t)__builtin_amdgcn_sbfe((int)t, 8 * q + 6 + AT, 1), r, 0x6A);
   }
   return wave_xor(r);
 }
-
-// The chunk's value from its eight shares' values v[w] (in LDS): 256 pairs
-// of a share and a bit, four per lane, each a column of F^(kSub (7 - w)).
 template <uint32_t BASE>
-__device__ __forceinline__ uint32_t mc_join(uint32_t v_lane, uint32_t lane) {
+__device__ __forceinline__ uint32_t mc_fold(const v16f &acc, uint32_t lane) {
+  return mc_share<1>(mc_parities(acc), [&](int q) {
+    return *reinterpret_cast<const uint4 *>(lds_at(BASE + kMcLane + 1024u * q + 16u * lane));
+  });
+}
+
+// The chunk's value from its eight shares' values: 256 pairs of a share and
+// a bit, four per lane, each a column c of F^(kSub (7 - w)) (CrcTables::mc_wave).
+__device__ __forceinline__ uint32_t mc_join(uint32_t v_lane, const uint4 &c, uint32_t lane) {
   // v_lane: the value of share lane / 8
-  const uint4 c = *reinterpret_cast<const uint4 *>(lds_at(BASE + kMcWave + 16u * lane));
   const uint32_t b = v_lane >> (4u * (lane & 7u));
   uint32_t r = c.x & (0u - (b & 1u));
   r = __builtin_amdgcn_bitop3_b32(c.y, (uint32_t)__builtin_amdgcn_sbfe((int)b, 1, 1), r, 0x6A);
@@ -485,14 +498,17 @@ __device__ __forceinline__ uint32_t mc_join(uint32_t v_lane, uint32_t lane) {
   r = __builtin_amdgcn_bitop3_b32(c.w, (uint32_t)__builtin_amdgcn_sbfe((int)b, 3, 1), r, 0x6A);
   return wave_xor(r);
 }
+template <uint32_t BASE>
+__device__ __forceinline__ uint32_t mc_join(uint32_t v_lane, uint32_t lane) {
+  return mc_join(v_lane, *reinterpret_cast<const uint4 *>(lds_at(BASE + kMcWave + 16u * lane)), lane);
+}
 
 // CRC of a 16-byte message of four uniform words (k = T.k_msg16), or of a
-// 12-byte one with w0 = 0 (k = T.k_msg12): lane l takes bits 2l and 2l + 1.
+// 12-byte one with w0 = 0 (k = T.k_msg12): lane l takes bits 2l and 2l + 1
+// with their columns c (CrcTables::mc_msg).
 // (A chain of 16 or 12 dependent table lookups otherwise.)
-template <uint32_t BASE>
 __device__ __forceinline__ uint32_t mc_msg(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3,
-                                           uint32_t k, uint32_t lane) {
-  const uint2 c = *reinterpret_cast<const uint2 *>(lds_at(BASE + kMcMsg + 8u * lane));
+                                           uint32_t k, const uint2 &c, uint32_t lane) {
   const uint32_t w = lane < 32u ? (lane < 16u ? w0 : w1) : (lane < 48u ? w2 : w3);
   const uint32_t b = w >> (2u * (lane & 15u));
   const uint32_t r = c.x & (0u - (b & 1u));
@@ -3275,21 +3291,26 @@ __global__ __launch_bounds__(kEncThreads) void k_huf_encode(EncArgs a, ChunkGeom
 // load issued before it).  A group whose streams overflow the stage, and the
 // last, short record, take a per-symbol path.  Checks and verdict bits are
 // the same as the per-workgroup decoders'.
-// Bound by latency (a table lookup in LDS per symbol) and, at 16 waves per
-// CU, by VALU issue (about 70% busy): so the CRC's 40 KiB of tables leave room
-// for 16 waves of 7.5 KiB (8 beside the byte tables' 90 KiB; a 3.5 KiB stage
-// holds streams of up to 6.8 bits a word), and an entry holds the symbol where
-// the word has it.  25,536 records (1.67 GB of bf16): 636 us (816 before),
-// 15 records: 51 us (58).
+// A table lookup in LDS per symbol is the serial chain of a wave, so what
+// counts is the waves in flight: 16 per CU at 128 VGPRs, of 8 KiB each, beside
+// the CRC's 32 KiB of row weights (8 fitted beside the byte tables' 90 KiB).
+// The CRC's small tables stay in device memory: a lane keeps each share's
+// parities and the shares fold together at the record's end.  With those
+// tables in LDS too the stage was 3.5 KiB, 6.8 bits a word, and a record
+// above that took the per-symbol path: 3,000 records of 7.6 bits 249 us to
+// receive, now 136; the 4 KiB stage holds 7.8 bits, past which little
+// is left below RAW.  (15 waves and all tables in LDS: 177 us against 149 for
+// 3,900 records, which 16 waves take in one round.)  An entry holds the symbol
+// where the word has it.
 constexpr int kHwWaves = 16;
 constexpr uint32_t kHwTab = 4096;    // per wave: decode table, 2^11 u16 entries
-constexpr uint32_t kHwStage = 3584;  // per wave: a group's streams (code order first)
+constexpr uint32_t kHwStage = 4096;  // per wave: a group's streams (code order first)
 constexpr uint32_t kHwOverrun = 64u * 11u / 8u + 8u;  // bytes a stream's reads may pass its end
-// the CRC tables, then the waves' decode tables (at multiples of 4096, so an
-// entry's address is the table's base ORed with it), then their stages
-constexpr uint32_t kLdsHwTab = (kMcBytes + 4095u) & ~4095u;
-constexpr uint32_t kLdsHwStage = kLdsHwTab + kHwWaves * kHwTab;
-constexpr uint32_t kLdsHufDecodeW = kLdsHwStage + kHwWaves * kHwStage;
+// the CRC's row weights, then each wave's decode table (at a multiple of 4096,
+// so an entry's address is the table's base ORed with it) and stage
+constexpr uint32_t kLdsHwTab = kMcLane;
+constexpr uint32_t kHwScratch = kHwTab + kHwStage;
+constexpr uint32_t kLdsHufDecodeW = kLdsHwTab + kHwWaves * kHwScratch;
 static_assert(kLdsHufDecodeW <= 163840, "record-per-wave decoder LDS fits one CU");
 
 __device__ __forceinline__ uint32_t buf4(Rsrc r, uint32_t off) {
@@ -3368,11 +3389,11 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
   const uint32_t r_hi = min(r1, n_rec), r_lo = min(r0, r_hi);
   const uint64_t table_off = ((uint64_t)uniform((uint32_t)(ctl->table_off >> 32)) << 32) |
                              uniform((uint32_t)ctl->table_off);
-  mc_load_tables<0>(g.crc_kind);
-  __syncthreads();  // the only barrier: the tables are in LDS
+  mc_load_tables<0, kMcLane>(g.crc_kind);
+  __syncthreads();  // the only barrier: the row weights are in LDS
   const CrcTables &T = g_tables[g.crc_kind];
   const uint32_t wave = uniform(threadIdx.x >> 6);
-  const uint32_t tbase = kLdsHwTab + wave * kHwTab, sbase = kLdsHwStage + wave * kHwStage;
+  const uint32_t tbase = kLdsHwTab + wave * kHwScratch, sbase = tbase + kHwTab;
   uint16_t *tab = reinterpret_cast<uint16_t *>(lds_at(tbase));
   uint8_t *sorted = lds_at(sbase);  // symbols in code order, while the table is built
   // (a workgroup's waves take records a grid apart: few records spread over
@@ -3398,7 +3419,8 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
     const bool tbad = c >= g.n_chunks || (r > 0 && prevc >= c) || (r == 0 && off != 64u) ||
                       (off & 15u) || off >= end || end > table_off ||
                       tile_order_bad(g, c, r == 0, has_next, nextc);
-    const uint32_t ec = mc_msg<0>(ew[0], ew[1], ew[2], ew[3], T.k_msg16, lane);
+    const uint2 mcol = *reinterpret_cast<const uint2 *>(T.mc_msg[lane]);
+    const uint32_t ec = mc_msg(ew[0], ew[1], ew[2], ew[3], T.k_msg16, mcol, lane);
     if (lane == 0) ecrc[r] = ec;
     if (tbad) {
       if (lane == 0) atomicOr(&ctl->table_bad, 1u);
@@ -3418,7 +3440,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
       k = (hw[0] >> 8) & 255u;
       base = (hw[0] >> 16) & 255u;
       sb = hw[2];
-      if (mc_msg<0>(0u, hw[0], hw[1], hw[2], T.k_msg12, lane) != hw[3] || (hw[0] >> 24) || hw[1] != n) {
+      if (mc_msg(0u, hw[0], hw[1], hw[2], T.k_msg12, mcol, lane) != hw[3] || (hw[0] >> 24) || hw[1] != n) {
         st = 4;
       } else if (mode == 0) {
         if (k || base || sb || rl != raw_rec_size(n)) st = 4;
@@ -3451,6 +3473,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
     // fills 1.6, made the decode's traffic 1.178 times its bytes.
     const Rsrc rs = rsrc(rec + kHufHead, hufk ? (uint32_t)pad16(sb) : 0u);
     uint4 sq0[4] = {};
+    const uint32_t bias = T.mc_bias[lane];
     if (hufk) {
       const uint32_t nb0 = rec[16 + lane], nb1 = rec[16 + 64 + lane];
       const uint32_t ln[4] = {nb0 & 15u, nb0 >> 4, nb1 & 15u, nb1 >> 4};
@@ -3532,7 +3555,13 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
     const Rsrc rb = rsrc(rec + smo, (uint32_t)pad16(n));                       // plane B
     const Rsrc ra = rsrc(rec + 16, mode == 0 ? (uint32_t)pad16(n) : 0u);       // RAW plane A
     uint8_t *dst = staging + (uint64_t)r * kChunk;
-    uint32_t share = 0;  // the CRC value of group lane / 8's share
+    // the lane's parities of the groups' shares, two groups in a word
+    uint32_t par[4] = {0, 0, 0, 0};
+    auto keep = [&](uint32_t q, const v16f &cv) {
+      const uint32_t t = mc_parities(cv) >> (q & 1u);
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) par[i] |= (q >> 1) == i ? t : 0u;
+    };
     const bool dec = hufk && hok;
     const bool full = n == kChunk / 2;
     if (!dec) {
@@ -3542,7 +3571,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
         uint2 pa[8], pb[8];
         uint32_t l16 = lane16;  // (the weights' reads stay in the loop)
         asm volatile("" : "+v"(l16));
-        v16f cv = mc_begin<0>(lane);
+        v16f cv = mc_start(T.mc_bias[lane]);
 #pragma unroll
         for (int h = 0; h < 8; ++h) {
           const uint32_t w0 = (8u * q + h) * 512u + 8u * lane;
@@ -3552,8 +3581,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
 #pragma unroll
         for (int h = 0; h < 8; ++h)
           hw_row_out<V3>(pa[h], pb[h], (8u * q + h) * 512u + 8u * lane, n, full, len, dst, cv, h, l16);
-        const uint32_t v = mc_fold<0>(cv, lane);
-        share = (lane >> 3) == q ? v : share;
+        keep(q, cv);
       }
     } else {
       // ---- Huffman streams: group q's bytes [A, A + 4096) staged as 4 KiB
@@ -3565,8 +3593,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
       uint32_t sob = 0;  // the group's first byte
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (1024u * i + lane16 < kHwStage)
-          *reinterpret_cast<uint4 *>(lds_at(sbase + 1024u * i + lane16)) = sq0[i];
+        *reinterpret_cast<uint4 *>(lds_at(sbase + 1024u * i + lane16)) = sq0[i];
       wave_sync();
 #pragma unroll 1
       for (uint32_t q = 0; q < 8u; ++q) {
@@ -3576,8 +3603,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
         sob += uniform(__builtin_amdgcn_readlane(incl, 63));  // the next group's
         // in the stage, with room for the reads of a stream that overruns
         // its bytes (64 codes of at most 11 bits and a dword ahead)
-        const bool fits =
-            sob - A <= kHwStage - kHwOverrun;
+        const bool fits = sob - A <= kHwStage - kHwOverrun;
         const bool more = q < 7u;
         uint2 pb[8];
 #pragma unroll
@@ -3602,7 +3628,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
         int32_t nb;
         uint32_t l16 = lane16;
         asm volatile("" : "+v"(l16));
-        v16f cv = mc_begin<0>(lane);
+        v16f cv = mc_start(bias);
         uint32_t pos = soq - A;
         const uint32_t pos0 = pos;
         if (fits && full) {
@@ -3699,10 +3725,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
             hw_row_out<V3>(make_uint2(a8[0], a8[1]), pb[h], w0, n, full, len, dst, cv, h, l16);
           }
         }
-        {
-          const uint32_t v = mc_fold<0>(cv, lane);
-          share = (lane >> 3) == q ? v : share;
-        }
+        keep(q, cv);
         // exactly the stream's bytes, the last one's unused bits zero
         const uint32_t used = 8u * (pos - pos0) - (uint32_t)nb;
         if ((used + 7u) / 8u != sbl) bad = true;
@@ -3711,8 +3734,7 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
           wave_sync();
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (1024u * i + lane16 < kHwStage)
-              *reinterpret_cast<uint4 *>(lds_at(sbase + 1024u * i + lane16)) = sq[i];
+            *reinterpret_cast<uint4 *>(lds_at(sbase + 1024u * i + lane16)) = sq[i];
           wave_sync();
           A = an;
         }
@@ -3727,7 +3749,19 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
         rec[kHufHead + sb + lane - 32u])
       bad = true;
     // ---- the record's CRC against its receipt
-    const uint32_t crc = finish_crc(mc_join<0>(share, lane), len, g, T);
+    uint4 col[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) col[i] = *reinterpret_cast<const uint4 *>(T.mc_lane[i][lane]);
+    const uint4 wcol = *reinterpret_cast<const uint4 *>(&T.mc_wave[0][0] + 4u * lane);
+    uint32_t share = 0;  // the value of group lane / 8's share
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const auto c = [&](int q) { return col[q]; };
+      const uint32_t v0 = mc_share<1>(par[i], c), v1 = mc_share<0>(par[i], c);
+      share = (lane >> 3) == 2u * i ? v0 : share;
+      share = (lane >> 3) == 2u * i + 1u ? v1 : share;
+    }
+    const uint32_t crc = finish_crc(mc_join(share, wcol, lane), len, g, T);
     const uint32_t stf = __ballot(bad) ? 4u : (crc != ew[1] ? 8u : 0u);
     if (lane == 0) {
       if (rec_status) rec_status[r] = stf;
