@@ -406,8 +406,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 constexpr uint32_t kMcLane = 32768, kMcWave = kMcLane + 4096, kMcBias = kMcWave + 1024;
 constexpr uint32_t kMcBytes = kMcBias + 256;
 
-// BYTES: all of them, or mc_b alone (kMcLane).
-template <uint32_t BASE, uint32_t BYTES = kMcBytes>
+template <uint32_t BASE>
 __device__ __forceinline__ void mc_load_tables(uint32_t kind) {
   static_assert(offsetof(CrcTables, mc_lane) - offsetof(CrcTables, mc_b) == kMcLane &&
                     offsetof(CrcTables, mc_wave) - offsetof(CrcTables, mc_b) == kMcWave &&
@@ -417,7 +416,7 @@ __device__ __forceinline__ void mc_load_tables(uint32_t kind) {
                 "mc_b .. mc_bias copied as one block");
   const uint4 *src = reinterpret_cast<const uint4 *>(&g_tables[kind].mc_b[0][0][0]);
   uint4 *dst = reinterpret_cast<uint4 *>(lds_at(BASE));
-  for (uint32_t i = threadIdx.x; i < BYTES / 16u; i += blockDim.x) dst[i] = src[i];
+  for (uint32_t i = threadIdx.x; i < kMcBytes / 16u; i += blockDim.x) dst[i] = src[i];
 }
 
 // The accumulators of a share before its first row.
@@ -3381,7 +3380,8 @@ __device__ __forceinline__ void hw_row_out(const uint2 &pa, const uint2 &pb, uin
 template <bool V3>
 __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
     const uint8_t *__restrict__ payload, ChunkGeom g, uint8_t *__restrict__ staging,
-    uint32_t *__restrict__ rec_status, uint8_t *ws, WsLayout L, uint32_t r0, uint32_t r1) {
+    uint32_t *__restrict__ rec_status, uint8_t *ws, WsLayout L, uint32_t r0, uint32_t r1,
+    uint32_t n_waves) {
   WsCtl *ctl = reinterpret_cast<WsCtl *>(ws + L.ctl);
   uint32_t *ecrc = reinterpret_cast<uint32_t *>(ws + L.entry_crc);
   if (!uniform(ctl->hdr_ok)) return;
@@ -3389,16 +3389,29 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
   const uint32_t r_hi = min(r1, n_rec), r_lo = min(r0, r_hi);
   const uint64_t table_off = ((uint64_t)uniform((uint32_t)(ctl->table_off >> 32)) << 32) |
                              uniform((uint32_t)ctl->table_off);
-  mc_load_tables<0, kMcLane>(g.crc_kind);
-  __syncthreads();  // the only barrier: the row weights are in LDS
   const CrcTables &T = g_tables[g.crc_kind];
+  {
+    // the row weights, in one round of loads from 256 threads on
+    const Rsrc rt = rsrc(&T.mc_b[0][0][0], kMcLane);
+    for (uint32_t i = 16u * threadIdx.x; i < kMcLane; i += 128u * blockDim.x) {
+      uint4 v[8];
+#pragma unroll
+      for (uint32_t j = 0; j < 8u; ++j) v[j] = buf16(rt, i + 16u * j * blockDim.x);
+#pragma unroll
+      for (uint32_t j = 0; j < 8u; ++j)
+        if (i + 16u * j * blockDim.x < kMcLane)
+          *reinterpret_cast<uint4 *>(lds_at(i + 16u * j * blockDim.x)) = v[j];
+    }
+  }
+  __syncthreads();  // the only barrier: the row weights are in LDS
   const uint32_t wave = uniform(threadIdx.x >> 6);
+  if (wave >= n_waves) return;  // (it only copied weights: no scratch of its own)
   const uint32_t tbase = kLdsHwTab + wave * kHwScratch, sbase = tbase + kHwTab;
   uint16_t *tab = reinterpret_cast<uint16_t *>(lds_at(tbase));
   uint8_t *sorted = lds_at(sbase);  // symbols in code order, while the table is built
   // (a workgroup's waves take records a grid apart: few records spread over
   // the CUs, a wave each, instead of filling the first ones)
-  for (uint32_t r = r_lo + blockIdx.x + gridDim.x * wave; r < r_hi; r += gridDim.x * kHwWaves) {
+  for (uint32_t r = r_lo + blockIdx.x + gridDim.x * wave; r < r_hi; r += gridDim.x * n_waves) {
     // (what derives from the lane is formed per record, not kept across them)
     uint32_t lane = threadIdx.x & 63u;
     asm volatile("" : "+v"(lane));
@@ -4344,17 +4357,19 @@ int launch_decode_records_v2(const void *payload, const ChunkGeom &g, void *stag
                              uint32_t r0, uint32_t r1, void *stream) {
   if (r1 <= r0 || !g.n_chunks) return 0;
   const uint32_t recs = min(r1 - r0, g.n_chunks);
+  // Records spread over the CUs first (15 records as 15 workgroups: 51 us, as
+  // two of eight waves 58), then over a workgroup's waves, which has the LDS
+  // of its decoding waves only: up to 6 waves (1,536 records on 256 CUs) leave
+  // room on the CU for another stream's workgroups.  Eight sessions of 400
+  // records decode in 616 us; with 16 waves' LDS whatever the count 775, with
+  // a workgroup per eight records 625.  Four waves at least copy the weights.
   const uint32_t grid = min((uint32_t)n_cu, recs);
-  if (g.codec == 3)
-    hipLaunchKernelGGL(k_huf_decode_w<true>, dim3(grid), dim3(64 * kHwWaves), kLdsHufDecodeW,
-                       S(stream), static_cast<const uint8_t *>(payload), g,
-                       static_cast<uint8_t *>(staging), rec_status, static_cast<uint8_t *>(ws), L, r0,
-                       r1);
-  else
-    hipLaunchKernelGGL(k_huf_decode_w<false>, dim3(grid), dim3(64 * kHwWaves), kLdsHufDecodeW,
-                       S(stream), static_cast<const uint8_t *>(payload), g,
-                       static_cast<uint8_t *>(staging), rec_status, static_cast<uint8_t *>(ws), L, r0,
-                       r1);
+  const uint32_t waves = min((uint32_t)kHwWaves, (recs + grid - 1u) / grid);
+  const uint32_t threads = 64u * max(waves, 4u), lds = kLdsHwTab + waves * kHwScratch;
+  hipLaunchKernelGGL(g.codec == 3 ? k_huf_decode_w<true> : k_huf_decode_w<false>, dim3(grid),
+                     dim3(threads), lds, S(stream), static_cast<const uint8_t *>(payload), g,
+                     static_cast<uint8_t *>(staging), rec_status, static_cast<uint8_t *>(ws), L, r0,
+                     r1, waves);
   return (int)hipGetLastError();
 }
 

@@ -428,3 +428,13 @@ def test_wide_streams_take_the_staged_path(wm, codec):
         best[symbols] = min(times)
     say(f"[v{codec}] decode of {n} bytes: 40 symbols {best[40]:.3f} ms, 150 {best[150]:.3f} ms")
     assert best[150] < 1.5 * best[40]
+
+
+@pytest.mark.parametrize("records", [2, 256, 512, 513, 1025, 3841])
+def test_record_counts_at_launch_shapes(wm, codec, records):
+    """Record counts on both sides of another wave per workgroup; the last
+    record short."""
+    n = records * CH - 2 * (records % 1000)
+    spec = wm_inputs.CacheSpec("shapes", (1, 2, 1, -(-n // 512), 128), seed=records)
+    state = host_bytes(wm_inputs.make_cache(spec, "cuda"))[:n].copy()
+    ship(wm, state, 0, f"{records} records", codec)
