@@ -161,7 +161,8 @@ int launch_fill_all(uint32_t *idx, uint32_t *n_out, uint32_t n, void *stream);
 // of the staged records (gs: the staged bytes as one state), receipts in
 // place of the chunks the install overwrites, their combined global CRC
 // against the header's; a failure ORs 32 into the verdict.  Uses the
-// workspace's control block, entry CRC and flag arrays.
+// workspace's control block, look-back words (a list of the chunks that
+// stay), entry CRC and flag arrays.
 int launch_reverify(const void *live, const ChunkGeom &g, const void *staging,
                     const ChunkGeom &gs, const void *payload, uint32_t *verdict, void *ws,
                     const WsLayout &L, int n_cu, void *stream);

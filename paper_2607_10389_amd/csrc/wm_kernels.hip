@@ -4174,8 +4174,9 @@ int launch_fill_all(uint32_t *idx, uint32_t *n_out, uint32_t n, void *stream) {
 // ascending list (idx[n_chunks] is its length): only their CRCs enter the
 // resulting state's.  The table of a verified payload is strictly ascending;
 // one that is not (changed since) lists every chunk.  Wave w of the single
-// workgroup writes the gaps before records w, w + 16, ...: chunk c between
-// records r - 1 and r has c - r uncovered chunks before it.
+// workgroup writes the gaps before records 64 w .. 64 w + 63, and on in
+// strides of 1024: chunk c between records r - 1 and r has c - r uncovered
+// chunks before it.
 __global__ __launch_bounds__(1024) void k_uncovered(const uint8_t *__restrict__ payload,
                                                     uint32_t n_chunks, uint32_t *__restrict__ idx) {
   const uint32_t n_rec = ld_u32(payload + 24);
@@ -4214,8 +4215,8 @@ __global__ __launch_bounds__(1024) void k_uncovered(const uint8_t *__restrict__ 
 }
 
 // Re-verifying install (Table 1: commit re-verifies, then swaps).  live_crc
-// holds the CRC of every chunk of live that no record overwrites, staged_crc that of every staged
-// record.  One workgroup walks the payload's table: a staged record whose
+// holds the CRC of every chunk of live that no record overwrites (the others'
+// may be there or not), staged_crc that of every staged record.  One workgroup walks the payload's table: a staged record whose
 // CRC differs from its receipt sets the flag, and the record's receipt
 // replaces the CRC of the chunk it will overwrite, so that live_crc becomes
 // the chunk CRCs of the state the install would produce.
@@ -4256,8 +4257,17 @@ int launch_reverify(const void *live, const ChunkGeom &g, const void *staging,
   uint32_t *staged_crc = reinterpret_cast<uint32_t *>(wsb + L.entry_crc);
   uint32_t *words = reinterpret_cast<uint32_t *>(wsb + L.ctl);  // [0] flag, [1] global
   int rc = 0;
-  if (g.n_chunks) {
-    // (the list lies where the look-back words and the staged table would)
+  // The list of the chunks that stay takes one workgroup 10 us and, where the
+  // gaps are long, 0.6 us more per 1,000 chunks; it saves a read of 9 ns per
+  // record.  Under this line every chunk is checksummed.  (The list whatever
+  // the counts: 24 records of 6,000 chunks 216 -> 234 us, 1,800 321 -> 323,
+  // 3,600 427 -> 411; 2,554 of 25,536 560 -> 563, 7,660 849 -> 809.)
+  const bool listed = gs.n_chunks > 2048u + g.n_chunks / 12u;
+  if (!listed) {
+    rc = launch_checksum(live, g, live_crc, nullptr, n_cu, stream, true);
+    if (rc) return rc;
+  } else {
+    // (the list lies where the look-back words would)
     uint32_t *list = reinterpret_cast<uint32_t *>(wsb + L.status);
     hipLaunchKernelGGL(k_uncovered, dim3(1), dim3(1024), 0, S(stream),
                        static_cast<const uint8_t *>(payload), g.n_chunks, list);

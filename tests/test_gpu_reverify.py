@@ -165,3 +165,77 @@ def test_reverify_reads_the_chunks_that_stay(wm, n_chunks, dirty):
         live = prev.clone()
         _check(m, live, 0, wm.WM_VERIFY_FAILED, "table out of order")
         assert torch.equal(live, prev)
+
+
+def _step(n_chunks, stay, kind=0):
+    """A decoded step that ships every chunk but `stay`, its last one short."""
+    from paper_2607_10389_amd import Mover
+    n = (n_chunks - 1) * CH + 4098
+    dirty = sorted(set(range(n_chunks)) - set(stay))
+    prev, cur = _pair(n_chunks + len(stay), n, [])
+    for c in dirty:
+        cur[c * CH + 9] ^= 1
+    m = Mover(n, kind)
+    m.encode_step(cur, prev)
+    m.decode()
+    torch.cuda.synchronize()
+    assert m.dirty_host().tolist() == dirty
+    return m, prev, cur, dirty
+
+
+def _written_words(m, live):
+    """Workspace words that a re-verifying install of `live` changes."""
+    m.ws_dst.fill_(0xA5)
+    st = m.commit_reverify(live)
+    torch.cuda.synchronize()
+    words = m.ws_dst[:m.ws_dst.numel() // 4 * 4].view(-1, 4)
+    return st, int((words != 0xA5).any(1).sum())
+
+
+@pytest.mark.parametrize("n_chunks,records", [(1500, 1), (1500, 1400), (2400, 2248)])
+def test_reverify_of_few_records_makes_no_list(wm, n_chunks, records):
+    """Below the line where a list of the chunks that stay pays, an install
+    writes the CRC of every chunk and staged record and the control words,
+    and no list."""
+    m, prev, cur, dirty = _step(n_chunks, range(n_chunks - records))
+    st, words = _written_words(m, prev.clone())
+    assert st == wm.WM_OK
+    assert words <= n_chunks + records + 16, words
+
+
+# 2,400 chunks: a list from 2,249 records on
+@pytest.mark.parametrize("kind,stay", [
+    (0, list(range(151))),                       # 2,249 records, one long gap
+    (1, list(range(1, 302, 2))),                 # short gaps
+    (0, [0, 5, 6] + list(range(1000, 1100)) + [2399]),
+    (1, list(range(2249, 2399)) + [7, 9]),       # 2,248: no list
+    (0, [])])
+def test_reverify_on_both_sides_of_the_list(wm, kind, stay):
+    """The right base installs, a byte flipped in a chunk that stays is
+    refused.  Where the table has changed since it was verified (two entries
+    and their staged records swapped: every record still matches its receipt)
+    the outcome depends on the chunks that were checksummed, and equals the
+    oracle's."""
+    m, prev, cur, dirty = _step(2400, stay, kind)
+    n = prev.numel()
+
+    def check(want, label, flip=None):
+        m.verdict.zero_()
+        live = prev.clone()
+        if flip is not None:
+            live[min(flip * CH + CH - 1, n - 1)] ^= 1
+        before = live.clone()
+        _check(m, live, kind, want, label)
+        assert torch.equal(live, cur if want == wm.WM_OK else before), label
+
+    check(wm.WM_OK, "right base")
+    for c in sorted({stay[0], stay[len(stay) // 2], stay[-1]}) if stay else []:
+        check(wm.WM_VERIFY_FAILED, f"chunk {c}", c)
+    at = int(m.payload_bytes.item()) - 16 * len(dirty)
+    for buf, a, b in ((m.payload, at + 16, 16), (m.staging, CH, CH)):
+        t = buf[a - b:a].clone()
+        buf[a - b:a] = buf[a:a + b]
+        buf[a:a + b] = t
+    check(wm.WM_OK, "two records swapped")
+    if stay:
+        check(wm.WM_VERIFY_FAILED, "two records swapped, another base", stay[-1])
