@@ -79,8 +79,8 @@ typedef int32_t wm_status;
  * wm_encode_step_static (format v1 only).  Formats v2 and v3 have no
  * single-pass step: their wm_encode_step takes the dirty list and every
  * chunk's CRC from one read of cur and prev, then runs the list encoder (same
- * outputs; without prev the encoder's own read gives the CRCs), and their
- * pre-copy rounds checksum every chunk. */
+ * outputs; without prev the encoder's own read gives the CRCs), and so do
+ * their pre-copy rounds. */
 #define WM_CODEC_EXPFOR 1
 #define WM_CODEC_EXPHUF 2
 #define WM_CODEC_BYTEPLANE 3
@@ -408,8 +408,9 @@ typedef struct {
  *              buffers left them; the round then runs wm_diff_dirty and
  *              checksums and encodes only the dirty chunks (each record's
  *              receipt and bytes from one read), and the header's global CRC
- *              combines kept and new CRCs.  After a round that did not return
- *              WM_OK, pass 0.  Chunks above 64 KiB: ignored (the kept chunk
+ *              combines kept and new CRCs (formats v2 and v3: the dirty list
+ *              and every chunk's CRC come from one read, whether 0 or 1).
+ *              After a round that did not return WM_OK, pass 0.  Chunks above 64 KiB: ignored (the kept chunk
  *              CRCs cannot give the tile receipts; every tile is checksummed).
  * Errors: those of the four calls it makes (WM_ERR_INVALID_ARG for a
  *         missing buffer, WM_ERR_CAPACITY for a short payload or staging,

@@ -637,27 +637,31 @@ wm_status wm_precopy_round(const void *cur, void *shipped, void *dest, uint64_t 
                        stream);
     if (s != WM_OK) return s;
   } else {
-    // the CRCs of clean chunks are those of shipped, kept from earlier
-    // rounds: diff, then checksum and encode only the dirty chunks (each
-    // CRC from the same read as its record)
-    s = wm_diff_dirty(cur, shipped, nbytes, p, b->dirty_idx, b->n_dirty, b->ws_src,
-                      b->ws_src_bytes, stream);
-    if (s != WM_OK) return s;
     int n_cu0 = 0;
     if ((s = ensure_device(&n_cu0)) != WM_OK) return s;
     n_cu0 = stream_cus(stream, n_cu0);
     const WsLayout L = ws_layout(g.n_chunks);
     if (g.codec != WM_CODEC_EXPFOR) {
-      // format v2 takes its receipts from a checksum of every chunk
-      if (launch_checksum(cur, g, b->crc, nullptr, n_cu0, stream) != 0 ||
+      // format v2 takes its receipts from a checksum of every chunk, made of
+      // the same read as the dirty list: the CRC of a chunk that a writer
+      // changes meanwhile is of the bytes that were compared.  (One read of
+      // cur less than a diff and a checksum.)
+      if (launch_scan(cur, shipped, g, b->crc, b->dirty_idx, b->n_dirty, b->ws_src, L, n_cu0,
+                      stream) != 0 ||
           launch_encode_v2(cur, g, b->dirty_idx, b->n_dirty, b->crc, nullptr, b->global_crc,
-                           b->payload, b->payload_bytes, b->ws_src, L, n_cu0,
-                           stream) != 0)
+                           b->payload, b->payload_bytes, b->ws_src, L, n_cu0, stream) != 0)
         return WM_ERR_HIP;
-    } else if (launch_encode(0, cur, nullptr, g, b->dirty_idx, b->n_dirty, nullptr, b->crc,
-                             b->global_crc, nullptr, nullptr, b->payload, b->payload_bytes,
-                             b->ws_src, L, n_cu0, stream) != 0) {
-      return WM_ERR_HIP;
+    } else {
+      // the CRCs of clean chunks are those of shipped, kept from earlier
+      // rounds: diff, then checksum and encode only the dirty chunks (each
+      // CRC from the same read as its record)
+      s = wm_diff_dirty(cur, shipped, nbytes, p, b->dirty_idx, b->n_dirty, b->ws_src,
+                        b->ws_src_bytes, stream);
+      if (s != WM_OK) return s;
+      if (launch_encode(0, cur, nullptr, g, b->dirty_idx, b->n_dirty, nullptr, b->crc,
+                        b->global_crc, nullptr, nullptr, b->payload, b->payload_bytes, b->ws_src,
+                        L, n_cu0, stream) != 0)
+        return WM_ERR_HIP;
     }
   }
   s = wm_decode_verify(b->payload, b->payload_cap, nbytes, p, b->staging, b->staging_cap,

@@ -438,3 +438,42 @@ def test_record_counts_at_launch_shapes(wm, codec, records):
     spec = wm_inputs.CacheSpec("shapes", (1, 2, 1, -(-n // 512), 128), seed=records)
     state = host_bytes(wm_inputs.make_cache(spec, "cuda"))[:n].copy()
     ship(wm, state, 0, f"{records} records", codec)
+
+
+def test_v2_rounds_keep_the_crcs_of_what_was_compared(wm, codec):
+    """While another stream writes single bytes of the source, a round that
+    succeeds leaves the CRCs of what the destination now holds: a chunk
+    changed after it was found clean keeps the CRC of the bytes that were
+    compared (it is dirty in the next round)."""
+    chunks, batches, per = 2048, 400, 4
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    cur = torch.randint(0, 256, (chunks * CH,), generator=gen, device="cuda", dtype=torch.uint8)
+    shipped, dest = cur.clone(), cur.clone()
+    m = mover(cur.numel(), 0, codec)
+    st, nd = m.precopy_round(cur, shipped, dest)  # the kept CRCs
+    assert st == wm.WM_OK and nd == 0
+    at = torch.randperm(chunks, generator=gen, device="cuda")[:batches * per].view(batches, per)
+    at = at * CH + torch.randint(0, CH, (batches, per), generator=gen, device="cuda")
+    value = cur[at] ^ 1
+    writer = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(writer):
+        torch.cuda._sleep(20_000_000)  # the writes' launches lie behind it
+        for b in range(batches):
+            cur.index_copy_(0, at[b], value[b])
+    kept = []
+    while not writer.query() and len(kept) < 24:
+        st, nd = m.precopy_round(cur, shipped, dest)
+        if st == wm.WM_OK and nd:  # (rounds that end before the writes begin hold nothing)
+            kept.append((shipped.clone(), m.crc.clone(), nd))
+    writer.synchronize()
+    assert kept, "no round ran while the source was written"
+    for state, crc, nd in kept:
+        want, _ = oracle.checksum_chunks(0, host_bytes(state), CH, ORACLE_THREADS)
+        bad = np.nonzero(u32(crc)[:chunks] != want)[0]
+        assert bad.size == 0, (len(kept), nd, bad[:8].tolist())
+    say(f"[v{codec}] rounds beside the writer: {[k[2] for k in kept]} dirty")
+    while nd:
+        st, nd = m.precopy_round(cur, shipped, dest)
+        assert st == wm.WM_OK
+    assert torch.equal(dest, cur) and torch.equal(shipped, cur)
