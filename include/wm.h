@@ -265,8 +265,9 @@ wm_status wm_commit_or_abort(void *live, uint64_t nbytes, const wm_params *p,
  *     state: the destination's base is the source's last shipped snapshot.
  * Without it the guarantee of a dirty ship holds only relative to the base
  * the destination already had.  On failure WM_V_REVERIFY is ORed into
- * *verdict and live is untouched.  Costs a read of those chunks and of the staged
- * records (their CRCs) before the install.  Waits for the stream; returns
+ * *verdict and live is untouched.  Before the install it costs a read of the
+ * staged records and of the chunks of live that no record overwrites (of all of
+ * live where the records are few).  Waits for the stream; returns
  * WM_OK (installed) or WM_VERIFY_FAILED.
  *   live, staging, payload, verdict : as for wm_commit_or_abort (SCATTER)
  *   ws : workspace of ws_bytes >= wm_workspace_bytes() (chunk CRCs)
@@ -410,8 +411,8 @@ typedef struct {
  *              receipt and bytes from one read), and the header's global CRC
  *              combines kept and new CRCs (formats v2 and v3: the dirty list
  *              and every chunk's CRC come from one read, whether 0 or 1).
- *              After a round that did not return WM_OK, pass 0.  Chunks above 64 KiB: ignored (the kept chunk
- *              CRCs cannot give the tile receipts; every tile is checksummed).
+ *              After a round that did not return WM_OK, pass 0.  Chunks above
+ *              64 KiB: ignored (the kept chunk CRCs cannot give the tile receipts; every tile is checksummed).
  * Errors: those of the four calls it makes (WM_ERR_INVALID_ARG for a
  *         missing buffer, WM_ERR_CAPACITY for a short payload or staging,
  *         WM_ERR_WORKSPACE, WM_ERR_HIP). */

@@ -77,8 +77,6 @@ struct ChunkGeom {
   uint32_t tile_log2;   // log2(chunk_bytes / kChunk): 0 for 64 KiB chunks
   uint32_t hdr_n;       // chunks: ceil(nbytes / chunk_bytes)
 };
-// Bytes of the caller's chunk.
-inline uint32_t geom_chunk_bytes(const ChunkGeom &g) { return kChunk << g.tile_log2; }
 
 // Workspace layout (bytes from the workspace base).
 struct WsLayout {

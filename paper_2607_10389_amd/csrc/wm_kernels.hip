@@ -84,11 +84,6 @@ __device__ __forceinline__ uint2 buf8(Rsrc r, uint32_t off) {
   const v2u v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
   return make_uint2(v.x, v.y);
 }
-__device__ __forceinline__ uint3 buf12(Rsrc r, uint32_t off) {
-  typedef uint32_t v3u __attribute__((ext_vector_type(3)));
-  const v3u v = __builtin_amdgcn_raw_buffer_load_b96(r, off, 0, 0);
-  return make_uint3(v.x, v.y, v.z);
-}
 
 // Uniform read-only kernel inputs through the constant address space, which
 // the compiler serves with scalar loads (no vector-memory wait).
@@ -294,7 +289,7 @@ __device__ __forceinline__ uint32_t lane_merge(uint32_t v0, uint32_t v1, uint32_
 }
 
 // Lane shift: lane l's merged value covers bytes that lie 16 (63 - l) + 4
-// bytes before the end of its wave's share (see lane_value), so it enters the
+// bytes before the end of its wave's share (see lane_value_load), so it enters the
 // wave's value shifted by F^(16 (63 - l) + 4): a GF(2) matrix of its own,
 // applied from its 32 columns in LDS (eight 16-byte reads issued together;
 // columns 4q..4q+3 of lane l at kLdsLaneMat + 1024 q + 16 l).
@@ -328,22 +323,10 @@ __device__ __forceinline__ uint32_t wave_xor(uint32_t v) {
 }
 __device__ __forceinline__ uint32_t lane_fold(uint32_t u) { return wave_xor(lane_shift(u)); }
 
-// The lane's merged value of the wave's 8 rows (before its lane shift).
-__device__ __forceinline__ uint32_t lane_value(const uint4 (&d)[kRows], const GLane &gl) {
-  uint32_t v0 = d[0].x, v1 = d[0].y, v2 = d[0].z, v3 = d[0].w;
-#pragma unroll
-  for (int h = 1; h < kRows; ++h) {
-    v0 = g_step(v0, d[h].x, gl);
-    v1 = g_step(v1, d[h].y, gl);
-    v2 = g_step(v2, d[h].z, gl);
-    v3 = g_step(v3, d[h].w, gl);
-  }
-  return lane_merge(v0, v1, v2, v3);
-}
-
-// lane_value of d while the next chunk's rows load into dn (one load per
-// row step, so the memory pipe takes them between the LDS rounds); a short
-// chunk's straddling piece is refetched as in load_chunk.
+// The lane's merged value of the wave's 8 rows d (before its lane shift),
+// while the next chunk's rows load into dn (one load per row step, so the
+// memory pipe takes them between the LDS rounds); a short chunk's straddling
+// piece is refetched as in load_chunk.
 __device__ __forceinline__ uint32_t lane_value_load(const uint4 (&d)[kRows], const GLane &gl,
                                                     const uint8_t *__restrict__ nbase,
                                                     uint32_t nlen, const Lane &l,
@@ -521,10 +504,12 @@ constexpr uint32_t kLdsChecksum = kLdsChkPart + 4u * kWaves * 4u;
 
 // Chunk CRCs: each wave takes its share of chunk i while chunk i + 1 loads,
 // one barrier per chunk; wave i % 8 joins the shares of chunk i afterwards.
-// Bound by the HBM read: two workgroups fit a CU (38 KiB of LDS, at most 128
-// VGPRs), and the set-up is one 38 KiB copy.  1.67 GB in 251 us, 6,680 GB/s
-// (264 us with the byte tables, one workgroup per CU); 51 MB in 14.2 us
-// (17.4), 16 chunks in 6.4 us (10.0).
+// Bound by the HBM read where every workgroup has many chunks: two workgroups
+// fit a CU (38 KiB of LDS, at most 128 VGPRs).  1.67 GB in 251 us, 6,680 GB/s
+// (264 us with the byte tables, one workgroup per CU).  Smaller states pay for
+// the 38 KiB table copy of each workgroup and an uneven last round: 51 MB in
+// 14.2 us (17.4), 3,600 GB/s, where 785 chunks leave 512 workgroups one or
+// two each; 16 chunks in 6.4 us (10.0).
 // With `per_chunk` and chunks above 64 KiB, each tile's CRC is shifted past
 // the rest of its chunk and XORed into its chunk's entry (zeroed before the
 // launch): CRC(A|B) = F^|B|(CRC(A)) ^ CRC(B) is linear in the pieces' CRCs.
@@ -896,7 +881,7 @@ struct EncArgs {
 };
 
 struct EncShared {
-  uint32_t u[kThreads];      // lane values of the chunk's CRC (lane_value)
+  uint32_t u[kThreads];      // lane values of the chunk's CRC (lane_value_load)
   uint32_t dirty_w[kWaves];  // per-wave "differs from prev"
   alignas(16) uint32_t esc_w[kWaves];  // escapes per wave
   uint32_t crc;               // the chunk's CRC
@@ -1895,7 +1880,7 @@ struct DecShared {
 };
 static_assert(sizeof(DecShared) <= kLdsMiscBytes, "decoder scratch fits");
 constexpr uint32_t kLdsDecEsc = kLdsLow;  // + 16 B of read slack, inside the region
-// lane CRC values of a record (lane_value), double-buffered by record step
+// lane CRC values of a record (lane_value_load), double-buffered by record step
 constexpr uint32_t kLdsDecU = kLdsDecEsc + kWaves * kDecEscBytes + 256;
 static_assert(kLdsDecU + 2 * kThreads * 4 <= kLdsLow + kLdsLowBytes, "decoder low region fits");
 __device__ __forceinline__ uint32_t *dec_u(uint32_t b) {
@@ -2422,7 +2407,7 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
             for (int w = 0; w < kWaves; ++w) bad |= sh.bad[(i - 1) & 1][w];
             // the record's CRC from the data waves' lane values: lane l folds
             // lane l of the eight waves (F^kSub per wave), then the lane
-            // shifts (F^4 included) and their XOR (see lane_value)
+            // shifts (F^4 included) and their XOR (see lane_value_load)
             const uint32_t *u = dec_u((i - 1) & 1);
             uint32_t acc = u[l.lane];
 #pragma unroll
@@ -3298,7 +3283,8 @@ __global__ __launch_bounds__(kEncThreads) void k_huf_encode(EncArgs a, ChunkGeom
 // tables in LDS too the stage was 3.5 KiB, 6.8 bits a word, and a record
 // above that took the per-symbol path: 3,000 records of 7.6 bits 249 us to
 // receive, now 136; the 4 KiB stage holds 7.8 bits, past which little
-// is left below RAW.  (15 waves and all tables in LDS: 177 us against 149 for
+// is left below RAW.  25,536 records (1.67 GB of bf16) move 1.043 times
+// their bytes at about 0.8 of the rate that a copy reaches.  (15 waves and all tables in LDS: 177 us against 149 for
 // 3,900 records, which 16 waves take in one round.)  An entry holds the symbol
 // where the word has it.
 constexpr int kHwWaves = 16;
@@ -3597,9 +3583,10 @@ __global__ __launch_bounds__(64 * kHwWaves) void k_huf_decode_w(
         keep(q, cv);
       }
     } else {
-      // ---- Huffman streams: group q's bytes [A, A + 4096) staged as 4 KiB
-      // (lane l's 16 bytes of each KiB); the next group's loads are in
-      // flight while this one decodes and enter the stage after it
+      // ---- Huffman streams: group q's bytes from A (its first one's 16-byte
+      // unit) staged in 4 KiB (lane l's 16 bytes of each KiB, zeros past the
+      // group's end); the next group's loads are in flight while this one
+      // decodes and enter the stage after it
       const uint32_t s4 = k <= 8u ? 1u : 0u;  // 4 symbols per refill check, else 2
       const uint32_t *stg = reinterpret_cast<const uint32_t *>(lds_at(sbase));
       uint32_t A = 0;    // group 0 starts the section
@@ -4216,8 +4203,8 @@ __global__ __launch_bounds__(1024) void k_uncovered(const uint8_t *__restrict__ 
 
 // Re-verifying install (Table 1: commit re-verifies, then swaps).  live_crc
 // holds the CRC of every chunk of live that no record overwrites (the others'
-// may be there or not), staged_crc that of every staged record.  One workgroup walks the payload's table: a staged record whose
-// CRC differs from its receipt sets the flag, and the record's receipt
+// may be there or not), staged_crc that of every staged record.  One workgroup
+// walks the payload's table: a staged record whose CRC differs from its receipt sets the flag, and the record's receipt
 // replaces the CRC of the chunk it will overwrite, so that live_crc becomes
 // the chunk CRCs of the state the install would produce.
 __global__ __launch_bounds__(1024) void k_reverify_records(const uint8_t *__restrict__ payload,
