@@ -3283,7 +3283,7 @@ __global__ __launch_bounds__(kEncThreads) void k_huf_encode(EncArgs a, ChunkGeom
 // tables in LDS too the stage was 3.5 KiB, 6.8 bits a word, and a record
 // above that took the per-symbol path: 3,000 records of 7.6 bits 249 us to
 // receive, now 136; the 4 KiB stage holds 7.8 bits, past which little
-// is left below RAW.  25,536 records (1.67 GB of bf16) move 1.043 times
+// is left below RAW.  25,536 records (1.67 GB of bf16) move 1.05 times
 // their bytes at about 0.8 of the rate that a copy reaches.  (15 waves and all tables in LDS: 177 us against 149 for
 // 3,900 records, which 16 waves take in one round.)  An entry holds the symbol
 // where the word has it.
